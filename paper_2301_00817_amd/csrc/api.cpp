@@ -56,6 +56,8 @@ struct les_ctx {
   int num_cu = 256;
   int kc = 16;                 // k-chunk of the fused kernel
   double* coords = nullptr;    // padded coordinates (3 ghost layers), freed by les_metrics
+  double* prod = nullptr;      // tables of a product mesh (NULL otherwise)
+  ProdTab pt;                  // and their parts
   void* M = nullptr;           // metrics, 10 padded variables of the storage type
   double* inflow = nullptr;    // entrance target primitives (5, nth, nr)
   void* stage[3] = {nullptr, nullptr, nullptr};   // RK stage states (storage type; the
@@ -255,7 +257,7 @@ static size_t storage_size(const les_params* p) {
 
 static void free_all(les_ctx* c) {
   void* ptrs[] = {c->coords, c->M, c->inflow, c->stage[0], c->stage[1], c->stage[2], c->visc,
-                  c->dyn_scr, c->dyn_part, c->dyn, c->R, c->PT, c->part, c->adj, c->adj_stage,
+                  c->dyn_scr, c->dyn_part, c->dyn, c->prod, c->R, c->PT, c->part, c->adj, c->adj_stage,
                   c->maxbits, c->dt, c->flag};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
@@ -263,6 +265,7 @@ static void free_all(les_ctx* c) {
   c->stage[0] = c->stage[1] = c->stage[2] = nullptr;
   c->visc = nullptr;
   c->dyn_scr = nullptr; c->dyn_part = nullptr; c->dyn = nullptr;
+  c->prod = nullptr; c->pt = ProdTab();
   c->R = nullptr; c->PT = nullptr; c->part = nullptr;
   c->adj = nullptr; c->adj_stage = nullptr;
   c->maxbits = nullptr; c->dt = nullptr; c->flag = nullptr;
@@ -436,13 +439,26 @@ int les_metrics(les_ctx* c, double* metrics_out, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   int r = dalloc(c, &c->M, (size_t)10 * c->g.vs * storage_size(&c->p), "metrics");
   if (r != LES_OK) return r;
+  const size_t tab_bytes = prod_tab_doubles(c->g) * sizeof(double);
+  r = dalloc(c, (void**)&c->prod, tab_bytes, "product-mesh tables");
+  if (r != LES_OK) return r;
   hipError_t e;
   if (c->p.precision == LES_FP32_STORAGE)
-    e = launch_metrics<float>(c->coords, c->cg, (float*)c->M, c->g, metrics_out, s);
+    e = launch_metrics<float>(c->coords, c->cg, (float*)c->M, c->g, metrics_out, c->prod, c->flag, s);
   else
-    e = launch_metrics<double>(c->coords, c->cg, (double*)c->M, c->g, metrics_out, s);
+    e = launch_metrics<double>(c->coords, c->cg, (double*)c->M, c->g, metrics_out, c->prod, c->flag, s);
   if (e != hipSuccess) return hip_fail(c, e, "metrics kernel");
+  int general = 1;
+  HIP_TRY(c, hipMemcpyAsync(&general, c->flag, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIP_TRY(c, launch_reset(c->maxbits, c->flag, s));
   HIP_TRY(c, hipStreamSynchronize(s));
+  if (general) {
+    HIP_TRY(c, hipFree(c->prod));
+    c->prod = nullptr;
+    c->bytes -= tab_bytes;
+  } else {
+    c->pt = prod_tab(c->prod, c->g);
+  }
   HIP_TRY(c, hipFree(c->coords));
   c->bytes -= (size_t)3 * c->cg.vs * sizeof(double);
   c->coords = nullptr;
@@ -529,7 +545,7 @@ static int residual_into(les_ctx* c, T* Q, T* R_out, hipStream_t s) {
     const long k = prof_begin(c, s);
     e = launch_fused<T>(Q, (const T*)c->M, c->g, phys<T>(c), c->kc, FUSED_EPI_R, R_out, nullptr,
                         nullptr, 0.0, nullptr, c->ph64, nullptr, FUSED_LAG_NONE, nullptr, c->dyn,
-                        s);
+                        c->pt, s);
     prof_end(c, k, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "residual kernel");
@@ -651,8 +667,8 @@ static int rk5_steps(les_ctx* c, double* Qn, int nsteps, double dt_fixed, double
     // dt of this step: the first step reduces over Q^n here, later steps
     // take the maximum accumulated by the previous step's last stage
     if (cfl && n == 0) {
-      if (fp32) e = launch_lambda_max<double, float>(Qn, (const float*)c->M, c->g, c->ph64, c->maxbits, s);
-      else e = launch_lambda_max<double, double>(Qn, (const double*)c->M, c->g, c->ph64, c->maxbits, s);
+      if (fp32) e = launch_lambda_max<double, float>(Qn, (const float*)c->M, c->g, c->ph64, c->maxbits, c->pt, s);
+      else e = launch_lambda_max<double, double>(Qn, (const double*)c->M, c->g, c->ph64, c->maxbits, c->pt, s);
     }
     if (e == hipSuccess)
       e = launch_dt_finalize(c->maxbits, c->p.cfl, dt_fixed, c->dt, dt_out ? dt_out + n : nullptr,
@@ -685,7 +701,7 @@ static int rk5_steps(les_ctx* c, double* Qn, int nsteps, double dt_fixed, double
       const int lag = !lagv ? FUSED_LAG_NONE : (l == 0 ? FUSED_LAG_WRITE : FUSED_LAG_READ);
       const long k = prof_begin(c, s);
       e = launch_fused<T>(src, M, c->g, phys<T>(c), c->kc, epi, dst, Qn, q64, c->p.rk_alpha[l],
-                          c->dt, c->ph64, c->maxbits, lag, (T*)c->visc, c->dyn, s);
+                          c->dt, c->ph64, c->maxbits, lag, (T*)c->visc, c->dyn, c->pt, s);
       prof_end(c, k, s);
       src = dst;
     }
@@ -830,7 +846,7 @@ int les_rk5_step_vjp(les_ctx* c, double* Qn, double dt, const double* Qbar_np1, 
     if (e == hipSuccess)
       e = launch_fused<double>(X[l - 1], (const double*)c->M, c->g, c->ph64, c->kc, FUSED_EPI_RK,
                                X[l], Qn, nullptr, al[l - 1], c->dt, c->ph64, c->maxbits,
-                               FUSED_LAG_NONE, nullptr, nullptr, s);
+                               FUSED_LAG_NONE, nullptr, nullptr, c->pt, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "rk5 adjoint forward kernels");
   // reverse: b5 = Qbar^(n+1); b(l-1) = -alpha_l dt J(Q^(l-1))^T b(l);

@@ -58,6 +58,18 @@ struct Phys {
 template <typename T>
 struct Vec5 { T v[5]; };
 
+// Metric tables of a product mesh: x depends on i alone, y and z on (j, k)
+// alone (cylindrical jet meshes, Cartesian boxes), so that all ten metric
+// terms of a point follow from x_xi(i) and (y_eta, z_eta, y_zeta, z_zeta)(j, k)
+// (product_terms in physics.hpp).  FP64 in both precision forms.  x == NULL:
+// not a product mesh, the stored metric arrays are read instead.
+struct ProdTab {
+  const double* x = nullptr;    // [nx + 4]
+  const double* yz = nullptr;   // [nth + 4][nr + 4][4]
+};
+// The (j, k) table's stride between planes, in doubles.
+__host__ __device__ __forceinline__ int prod_plane(const Grid& g) { return (g.nr + 2 * NG) * 4; }
+
 // Sizes of the state arrays a kernel touches, per launch.
 inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 

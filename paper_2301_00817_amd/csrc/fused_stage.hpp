@@ -68,6 +68,39 @@ __device__ __forceinline__ void load_metrics(const T* M, const Grid& g, unsigned
   for (int c = 0; c < 10; ++c) m[c] = gld(M, g, c, k, col);
 }
 
+// Metric data of a column along the march: the ten stored terms of a plane,
+// or (product mesh) the plane's four (j, k) table values, expanded to the
+// terms where used.  col, row: the column's offset within a plane of the
+// metric arrays (bytes) and of the table (elements).
+template <typename T, bool PROD> struct MetData { using type = T; static constexpr int N = 10, NS = 9; };
+template <typename T> struct MetData<T, true> { using type = double; static constexpr int N = 4, NS = 4; };
+
+template <bool PROD, typename T, typename D>
+__device__ __forceinline__ void load_met(const T* M, const ProdTab& pt, const Grid& g, unsigned col,
+                                         int row, int k, D m[]) {
+  if constexpr (PROD) {
+    const double* p = pt.yz + (long long)(k + NG) * prod_plane(g);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) m[c] = p[row + c];
+  } else {
+    load_metrics(M, g, col, k, m);
+  }
+}
+
+// n = 10, or 9 without J^-1
+template <bool PROD, int n, typename T, typename D>
+__device__ __forceinline__ void met_terms(const D m[], double xx, T out[]) {
+  if constexpr (PROD) {
+    double w[10];
+    product_terms(xx, m, w);
+#pragma unroll
+    for (int c = 0; c < n; ++c) out[c] = (T)w[c];
+  } else {
+#pragma unroll
+    for (int c = 0; c < n; ++c) out[c] = m[c];
+  }
+}
+
 // Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  The
 // hardware id is remapped so that XCD x receives a contiguous run of tiles,
 // i fastest, then j, then the k-chunk: tiles that share halos run at the
@@ -117,12 +150,20 @@ template <> struct FusedOccE<float, EPI_RK_LAST> { static constexpr int waves = 
 // padded variables; LAG_READ takes them from there).  The tiling is the same
 // in every stage, so the points read are those written; points shared by
 // two blocks are written twice with the same value.
-template <typename T, int EPI, bool AXIS, int LAG, bool DYN>
+// PROD: product mesh.  The ten metric terms are formed from tables (four
+// FP64 values per (j, k), read once per plane by each row, one per i), which
+// spares 80 of the 200 bytes per point and stage (FP32: 40 of 128), the
+// registers of two planes of metric terms, and the arithmetic on the four
+// terms that are zero.  The terms and results are bitwise those of the general
+// form in FP64.  A step (with the first reduction of dt, which reads the same
+// tables): 36.7 -> 28.4 ms on 102 M points, 4.21 -> 3.61 ms for two on 5.9 M,
+// FP32 5.77 -> 4.83 ms on 23.6 M.
+template <typename T, int EPI, bool AXIS, int LAG, bool DYN, bool PROD>
 __global__ void __launch_bounds__(Tile<T>::X * Tile<T>::Y, (FusedOccE<T, EPI>::waves))
 k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_arg, int kc,
         TileMap tm, T* out, const double* Q0, double* Q64, double alpha,
         const double* __restrict__ dtp, Phys<double> ph64, unsigned long long* __restrict__ maxbits,
-        T* __restrict__ visc, const double* __restrict__ dyn) {
+        T* __restrict__ visc, const double* __restrict__ dyn, ProdTab ptab) {
   Phys<T> ph = ph_arg;
   if (DYN) {   // dynamic model: coefficients of this state, from the device
     ph.sgs_coef = (T)dyn[0];
@@ -198,7 +239,8 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   T Qd[5], Pd[5];        // Q and (u, v, w, T, p) at kk+1
   T Pb[5];               // (u, v, w, T, p) at kk-1
   T Qn[5];               // Q at kk+2, in flight
-  T met[10], metn[10];   // metrics at (i, j, kk) and the prefetch for kk+1
+  using MD = MetData<T, PROD>;
+  typename MD::type met[MD::N], metn[MD::N];   // metrics at (i, j, kk), prefetch for kk+1
   T lag[2], lagn[2];     // held (mu + mu_sgs, conductivity), same planes (LAG_READ)
   constexpr bool CS = EPI == EPI_RK_LAST;        // metric terms carried (above)
   constexpr bool DEFER = CS && sizeof(T) == 8;    // loads deferred to free registers
@@ -220,7 +262,11 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   T acc[5];              // RHS at kk-1 without its zeta face kk-1/2:
                          // in-plane faces minus the zeta face kk-3/2
   double lmax = 0.0;
-  T Sp[9];               // last stage: metric terms of plane kk-1
+  typename MD::type Sp[MD::NS];   // last stage: metric terms of plane kk-1
+  // product mesh: x_xi of the column, its row of the (j, k) table (columns
+  // beyond the padded box take the nearest point's, as for the state)
+  const double xx = PROD ? ptab.x[min(max(i, -NG), g.nx + NG - 1) + NG] : 0.0;
+  const int trow = (min(max(j, -NG), g.nr + NG - 1) + NG) * 4;
 
   {
     T q[5], pc[5];
@@ -238,7 +284,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     }
     load_q(Qin, g, oq, k0, Qd);
     prim5(Qd, ph, Pd);
-    load_metrics(M, g, oq, k0 - 1, met);
+    load_met<PROD>(M, ptab, g, oq, trow, k0 - 1, met);
     if (LAG == LAG_READ) load_lag(k0 - 1, lag);
   }
 #pragma unroll
@@ -261,7 +307,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     // ahead), in flight during (b)
     if (more) {
       if (!LATE_QN && kk + 2 <= k1 + 1) load_q(Qin, g, oq, kk + 2, Qn);
-      load_metrics(M, g, oq, kk + 1, metn);
+      load_met<PROD>(M, ptab, g, oq, trow, kk + 1, metn);
       if (LAG == LAG_READ) load_lag(kk + 1, lagn);
     }
     if (PQ0 && interior && kk - 1 >= k0) {
@@ -290,13 +336,17 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       neighbour_terms(m, pl, in.pr[4], in.dl[1], in.nu[1]);
       neighbour_terms(Pb, Pd, in.pr[4], in.dl[2], in.nu[2]);
     }
+    {
+      T m[10];
+      met_terms<PROD, 10>(met, xx, m);
 #pragma unroll
-    for (int d = 0; d < 3; ++d)
+      for (int d = 0; d < 3; ++d)
 #pragma unroll
-      for (int c = 0; c < 3; ++c) in.S[d][c] = met[3 * d + c];
-    in.V = met[9];
+        for (int c = 0; c < 3; ++c) in.S[d][c] = m[3 * d + c];
+      in.V = m[9];
+    }
     if (LAG == LAG_READ) { in.mt = lag[0]; in.kap = lag[1]; }
-    point_quantities<T, LAG, DYN>(in, ph, po);
+    point_quantities<T, LAG, DYN, PROD>(in, ph, po);
     if (LAG == LAG_WRITE && col_ok && ph.viscous) {
       gst(visc, g, 0, kk, oq, po.mt);
       gst(visc, g, 1, kk, oq, po.kap);
@@ -389,10 +439,12 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
           for (int c = 0; c < 5; ++c) q0[c] = PQ0 ? q0p[c] : gld(Q0, g, c, kk - 1, oq64);
         }
         if (EPI == EPI_RK_LAST) {
+          T m[9];
+          met_terms<PROD, 9>(Sp, xx, m);
 #pragma unroll
           for (int d = 0; d < 3; ++d)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) S[d][c] = (double)Sp[3 * d + c];
+            for (int c = 0; c < 3; ++c) S[d][c] = (double)m[3 * d + c];
         }
         const T iV = trcp(Vz);
         T R[5];
@@ -411,7 +463,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
             if (EPI == EPI_RK_LAST && Q64) gst(Q64, g, c, kk - 1, oq64, qn[c]);
           }
           if (EPI == EPI_RK_LAST) {
-            const double x = lambda_sum(qn, S, (double)Vz, ph64);
+            const double x = lambda_sum<PROD>(qn, S, (double)Vz, ph64);
             if (!(AXIS && axis_row) && (x != x || x > lmax)) lmax = x;
           }
         }
@@ -456,10 +508,10 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       prim5(Qd, ph, Pd);
       if (CS) {
 #pragma unroll
-        for (int c = 0; c < 9; ++c) Sp[c] = met[c];
+        for (int c = 0; c < MD::NS; ++c) Sp[c] = met[c];
       }
 #pragma unroll
-      for (int c = 0; c < 10; ++c) met[c] = metn[c];
+      for (int c = 0; c < MD::N; ++c) met[c] = metn[c];
       if (LAG == LAG_READ) { lag[0] = lagn[0]; lag[1] = lagn[1]; }
     }
   }
@@ -523,7 +575,7 @@ template <typename T>
 hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph, int kc, int epi,
                         T* out, const double* Q0, double* Q64, double alpha, const double* dt,
                         const Phys<double>& ph64, unsigned long long* maxbits, int lag, T* visc,
-                        const double* dyn, hipStream_t s) {
+                        const double* dyn, const ProdTab& pt, hipStream_t s) {
   if (ph.sgs == 3 && !dyn) return hipErrorInvalidValue;
   // instances: LAG_NONE with every epilogue, LAG_WRITE with EPI_RK (stage 1),
   // LAG_READ with EPI_RK and EPI_RK_LAST (stages 2-5)
@@ -538,14 +590,18 @@ hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph
   tm.per_xcd = (int)((ntiles + NXCD - 1) / NXCD);
   const dim3 grid((unsigned)(tm.per_xcd * NXCD));
   const dim3 block(Tile<T>::X, Tile<T>::Y, 1);
+#define LESJET_FUSED_P(E, A, L, D, P)                                                  \
+  hipLaunchKernelGGL((k_fused<T, E, A, L, D, P>), grid, block, 0, s, Q, M, g, ph, kc, tm, \
+                     out, Q0, Q64, alpha, dt, ph64, maxbits, visc, dyn, pt)
 #define LESJET_FUSED(E, A, L)                                                          \
   do {                                                                                 \
-    if (ph.sgs == 3)                                                                   \
-      hipLaunchKernelGGL((k_fused<T, E, A, L, true>), grid, block, 0, s, Q, M, g, ph, kc, tm, \
-                         out, Q0, Q64, alpha, dt, ph64, maxbits, visc, dyn);           \
-    else                                                                               \
-      hipLaunchKernelGGL((k_fused<T, E, A, L, false>), grid, block, 0, s, Q, M, g, ph, kc, tm, \
-                         out, Q0, Q64, alpha, dt, ph64, maxbits, visc, dyn);           \
+    if (ph.sgs == 3) {                                                                 \
+      if (pt.x) LESJET_FUSED_P(E, A, L, true, true);                                   \
+      else LESJET_FUSED_P(E, A, L, true, false);                                       \
+    } else {                                                                           \
+      if (pt.x) LESJET_FUSED_P(E, A, L, false, true);                                  \
+      else LESJET_FUSED_P(E, A, L, false, false);                                      \
+    }                                                                                  \
   } while (0)
 #define LESJET_FUSED_EPI(A)                                                        \
   if (lag == LAG_WRITE) LESJET_FUSED(EPI_RK, A, LAG_WRITE);                        \
@@ -562,6 +618,7 @@ hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph
   }
 #undef LESJET_FUSED_EPI
 #undef LESJET_FUSED
+#undef LESJET_FUSED_P
   return hipGetLastError();
 }
 

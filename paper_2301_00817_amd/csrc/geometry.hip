@@ -3,6 +3,7 @@
 // "Transformation of Coordinates": metric-term and Jacobian equations, the
 // eta row taken as the cofactor r_zeta x r_xi).
 #include "launch.hpp"
+#include "physics.hpp"
 
 namespace lesjet {
 
@@ -80,10 +81,33 @@ __global__ void k_coord_ghost(double* __restrict__ C, CGrid g, int dir, int lo_k
   }
 }
 
+// Tables of a product mesh (x of i, y and z of (j, k)) from the coordinates
+// of one row and one (j, k) plane; k_metrics decides whether they hold.
+__global__ void k_prod_tab(const double* __restrict__ C, CGrid cg, Grid g, double* __restrict__ yz,
+                           double* __restrict__ x) {
+  const int NR = g.nr + 2 * NG, NX = g.nx + 2 * NG, n = NR * (g.nth + 2 * NG);
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t < n) {
+    const int j = t % NR - NG, k = t / NR - NG;
+    const double* Y = C + (long long)cg.vs;
+    const double* Z = C + 2LL * cg.vs;
+    yz[4 * t + 0] = 0.5 * (Y[cg.at(0, j + 1, k)] - Y[cg.at(0, j - 1, k)]);
+    yz[4 * t + 1] = 0.5 * (Z[cg.at(0, j + 1, k)] - Z[cg.at(0, j - 1, k)]);
+    yz[4 * t + 2] = 0.5 * (Y[cg.at(0, j, k + 1)] - Y[cg.at(0, j, k - 1)]);
+    yz[4 * t + 3] = 0.5 * (Z[cg.at(0, j, k + 1)] - Z[cg.at(0, j, k - 1)]);
+  } else if (t < n + NX) {
+    const int i = t - n - NG;
+    x[t - n] = 0.5 * (C[cg.at(i + 1, 0, 0)] - C[cg.at(i - 1, 0, 0)]);
+  }
+}
+
 // Metrics at every point of the padded state box; T is the storage type.
+// *general is raised where the product-mesh tables do not give exactly the
+// stored terms (NaN among them).
 template <typename T>
 __global__ void k_metrics(const double* __restrict__ C, CGrid cg, T* __restrict__ M, Grid g,
-                          double* __restrict__ M64) {
+                          double* __restrict__ M64, ProdTab pt, int* __restrict__ general) {
+  bool same = true;
   const int NX = g.nx + 2 * NG, NR = g.nr + 2 * NG, NT = g.nth + 2 * NG;
   const long long tot = (long long)NX * NR * NT;
   for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < tot;
@@ -117,7 +141,11 @@ __global__ void k_metrics(const double* __restrict__ C, CGrid cg, T* __restrict_
     for (int c = 0; c < 10; ++c) M[(long long)c * g.vs + o] = (T)m[c];
     if (M64)
       for (int c = 0; c < 10; ++c) M64[(long long)c * g.vs + o] = m[c];
+    double mp[10];
+    product_terms(pt.x[i + NG], pt.yz + (long long)(k + NG) * prod_plane(g) + (j + NG) * 4, mp);
+    for (int c = 0; c < 10; ++c) same = same && (T)m[c] == (T)mp[c];
   }
+  if (!same) *general = 1;
 }
 
 static unsigned grid_stride_blocks(long long n) {
@@ -158,15 +186,20 @@ hipError_t launch_coords(const double* xyz, const double* tab, double* C, const 
 
 template <typename T>
 hipError_t launch_metrics(const double* C, const CGrid& cg, T* M, const Grid& g, double* M64,
-                          hipStream_t s) {
+                          double* tab, int* general, hipStream_t s) {
   const long long n = (long long)(g.nx + 2 * NG) * (g.nr + 2 * NG) * (g.nth + 2 * NG);
-  hipLaunchKernelGGL(k_metrics<T>, dim3(grid_stride_blocks(n)), dim3(256), 0, s, C, cg, M, g, M64);
+  const ProdTab pt = prod_tab(tab, g);
+  const int nt = (g.nr + 2 * NG) * (g.nth + 2 * NG) + g.nx + 2 * NG;
+  hipLaunchKernelGGL(k_prod_tab, dim3(blocks_for(nt, 256)), dim3(256), 0, s, C, cg, g, tab,
+                     tab + (pt.x - tab));
+  hipLaunchKernelGGL(k_metrics<T>, dim3(grid_stride_blocks(n)), dim3(256), 0, s, C, cg, M, g, M64, pt,
+                     general);
   return hipGetLastError();
 }
 
 template hipError_t launch_metrics<double>(const double*, const CGrid&, double*, const Grid&,
-                                           double*, hipStream_t);
+                                           double*, double*, int*, hipStream_t);
 template hipError_t launch_metrics<float>(const double*, const CGrid&, float*, const Grid&,
-                                          double*, hipStream_t);
+                                          double*, double*, int*, hipStream_t);
 
 }  // namespace lesjet

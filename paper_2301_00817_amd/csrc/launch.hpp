@@ -12,9 +12,21 @@ namespace lesjet {
 hipError_t launch_coords(const double* xyz, const double* tab, double* C, const CGrid& cg,
                          const int bc[6], const double period[3][3], hipStream_t s);
 
+// Metric terms on the padded box, and the tables of a product mesh (tab:
+// prod_tab_doubles(g), laid out as ProdTab by prod_tab); *general (device) is
+// raised if the tables do not reproduce every stored term exactly.
 template <typename T>
 hipError_t launch_metrics(const double* C, const CGrid& cg, T* M, const Grid& g, double* M64,
-                          hipStream_t s);
+                          double* tab, int* general, hipStream_t s);
+inline size_t prod_tab_doubles(const Grid& g) {
+  return (size_t)(g.nth + 2 * NG) * prod_plane(g) + (size_t)(g.nx + 2 * NG);
+}
+inline ProdTab prod_tab(const double* tab, const Grid& g) {
+  ProdTab pt;
+  pt.yz = tab;
+  pt.x = tab + (size_t)(g.nth + 2 * NG) * prod_plane(g);
+  return pt;
+}
 
 // Axis row j = 0 := azimuthal mean of row j = 1 (centerline through the nodes).
 template <typename T>
@@ -40,7 +52,7 @@ template <typename T>
 hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph, int kc, int epi,
                         T* out, const double* Q0, double* Q64, double alpha, const double* dt,
                         const Phys<double>& ph64, unsigned long long* maxbits, int lag, T* visc,
-                        const double* dyn, hipStream_t s);
+                        const double* dyn, const ProdTab& pt, hipStream_t s);
 
 // Dynamic Smagorinsky coefficients of the ghost-filled state Q: scratch SC
 // (DYN_SCRATCH_VARS padded FP64 variables), part (7 doubles per block of
@@ -61,7 +73,7 @@ enum { FUSED_LAG_NONE = 0, FUSED_LAG_WRITE = 1, FUSED_LAG_READ = 2 };
 
 template <typename TQ, typename TM>
 hipError_t launch_lambda_max(const TQ* Q, const TM* M, const Grid& g, const Phys<double>& ph,
-                             unsigned long long* maxbits, hipStream_t s);
+                             unsigned long long* maxbits, const ProdTab& pt, hipStream_t s);
 
 hipError_t launch_dt_finalize(unsigned long long* maxbits, double cfl, double dt_fixed,
                               double* dt, double* dt_out, int* flag, hipStream_t s);

@@ -141,6 +141,45 @@ __host__ __device__ __forceinline__ void prim5(const T q[5], const Phys<T>& ph, 
   pr[3] = ph.gamma * pr[4] * ir;
 }
 
+// Multiply-add of the dot products below, contracted by name: a product
+// mesh leaves out the terms that are exactly zero and keeps the order and
+// contraction of the others, so that it rounds as the general form does.
+__host__ __device__ __forceinline__ double tfma(double a, double b, double c) { return fma(a, b, c); }
+__host__ __device__ __forceinline__ float tfma(float a, float b, float c) { return fmaf(a, b, c); }
+// A product rounded by itself (never contracted into a following sum).
+template <typename T>
+__host__ __device__ __forceinline__ T rmul(T a, T b) {
+#pragma clang fp contract(off)
+  return a * b;
+}
+
+// Metric terms m[0..9] (S^xi, S^eta, S^zeta, J^-1) of a product mesh point from
+// x_xi and t = (y_eta, z_eta, y_zeta, z_zeta): the central-difference formulas of
+// k_metrics with x_eta = x_zeta = y_xi = z_xi = 0, rounded as there (k_metrics
+// checks that they agree at every point before a mesh is taken as a product).
+__host__ __device__ __forceinline__ void product_terms(double xx, const double t[4], double m[10]) {
+  m[0] = fma(t[0], t[3], -rmul(t[2], t[1]));
+  m[1] = m[2] = m[3] = m[6] = 0.0;
+  m[4] = rmul(t[3], xx);
+  m[5] = -rmul(xx, t[2]);
+  m[7] = -rmul(t[1], xx);
+  m[8] = rmul(xx, t[0]);
+  m[9] = fma(m[5], t[1], rmul(m[8], t[3]));
+}
+
+// S . a for row d of the metric terms; a product mesh has S^xi = (S, 0, 0) and
+// S^eta, S^zeta = (0, S, S).
+template <bool PROD, typename T>
+__host__ __device__ __forceinline__ T row_dot(int d, const T S[3], T a0, T a1, T a2) {
+  if (!PROD) return S[0] * a0 + S[1] * a1 + S[2] * a2;
+  return d == 0 ? rmul(S[0], a0) : tfma(S[2], a2, rmul(S[1], a1));
+}
+template <bool PROD, typename T>
+__host__ __device__ __forceinline__ T row_norm(int d, const T S[3]) {
+  if (!PROD) return tsqrt(S[0] * S[0] + S[1] * S[1] + S[2] * S[2]);
+  return d == 0 ? tabs(S[0]) : tsqrt(tfma(S[2], S[2], rmul(S[1], S[1])));
+}
+
 // Data a point needs: its state and primitives, the central differences of
 // (u, v, w, T) and the pressure sensors along the three index directions
 // (formed by the caller from the six neighbours, see `neighbour_terms`), its
@@ -207,7 +246,9 @@ enum { LAG_NONE = 0, LAG_WRITE = 1, LAG_READ = 2 };
 
 // DYN: the dynamic SGS model's terms are compiled in (used when ph.sgs == 3);
 // a separate instance so that the other models carry none of them.
-template <typename T, int LAG = LAG_NONE, bool DYN = false>
+// PROD: product mesh (the zero metric terms are not touched); separate for
+// the same reason.
+template <typename T, int LAG = LAG_NONE, bool DYN = false, bool PROD = false>
 __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phys<T>& ph,
                                                  PointOut<T>& out) {
   Prim<T> s;
@@ -218,15 +259,18 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
   const T aiV = tabs(iV);
 
   T Uc[3];
-  for (int d = 0; d < 3; ++d)
-    Uc[d] = in.S[d][0] * s.u + in.S[d][1] * s.v + in.S[d][2] * s.w;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) Uc[d] = row_dot<PROD>(d, in.S[d], s.u, s.v, s.w);
 
   // inviscid point fluxes
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
     out.G[d][0] = s.rho * Uc[d];
-    out.G[d][1] = in.q[1] * Uc[d] + s.p * in.S[d][0];
-    out.G[d][2] = in.q[2] * Uc[d] + s.p * in.S[d][1];
-    out.G[d][3] = in.q[3] * Uc[d] + s.p * in.S[d][2];
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+      if (PROD && (d == 0) != (m == 0)) out.G[d][1 + m] = rmul(in.q[1 + m], Uc[d]);
+      else out.G[d][1 + m] = in.q[1 + m] * Uc[d] + s.p * in.S[d][m];
+    }
     out.G[d][4] = (in.q[4] + s.p) * Uc[d];
   }
 
@@ -234,9 +278,17 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
     // chain rule on the central differences
     const T (&dl)[3][4] = in.dl;
     T g[4][3];   // g[f][m] = d phi_f / d x_m, phi = (u, v, w, T)
+#pragma unroll
     for (int f = 0; f < 4; ++f)
-      for (int m = 0; m < 3; ++m)
-        g[f][m] = (in.S[0][m] * dl[0][f] + in.S[1][m] * dl[1][f] + in.S[2][m] * dl[2][f]) * iV;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        if (!PROD)
+          g[f][m] = (in.S[0][m] * dl[0][f] + in.S[1][m] * dl[1][f] + in.S[2][m] * dl[2][f]) * iV;
+        else if (m == 0)
+          g[f][m] = rmul(in.S[0][0], dl[0][f]) * iV;
+        else
+          g[f][m] = tfma(in.S[2][m], dl[2][f], rmul(in.S[1][m], dl[1][f])) * iV;
+      }
 
     T mt, kap;
     if (LAG == LAG_READ) {
@@ -271,10 +323,11 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
       const T s2 = strain_sq(g);
       const T delta = tcbrt(tabs(in.V));
       const T psgs = ph.iso_coef * s.rho * delta * delta * (T(2) * s2);
+#pragma unroll
       for (int d = 0; d < 3; ++d) {
-        out.G[d][1] += psgs * in.S[d][0];
-        out.G[d][2] += psgs * in.S[d][1];
-        out.G[d][3] += psgs * in.S[d][2];
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+          if (!PROD || (d == 0) == (m == 0)) out.G[d][1 + m] += psgs * in.S[d][m];
         out.G[d][4] += psgs * Uc[d];
       }
     }
@@ -291,21 +344,20 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
     T beta[3];
     for (int j = 0; j < 3; ++j)
       beta[j] = tau[0][j] * s.u + tau[1][j] * s.v + tau[2][j] * s.w + kapc * g[3][j];
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
       const T* Sd = in.S[d];
-      out.G[d][1] -= Sd[0] * tau[0][0] + Sd[1] * tau[0][1] + Sd[2] * tau[0][2];
-      out.G[d][2] -= Sd[0] * tau[1][0] + Sd[1] * tau[1][1] + Sd[2] * tau[1][2];
-      out.G[d][3] -= Sd[0] * tau[2][0] + Sd[1] * tau[2][1] + Sd[2] * tau[2][2];
-      out.G[d][4] -= Sd[0] * beta[0] + Sd[1] * beta[1] + Sd[2] * beta[2];
+#pragma unroll
+      for (int m = 0; m < 3; ++m)
+        out.G[d][1 + m] -= row_dot<PROD>(d, Sd, tau[m][0], tau[m][1], tau[m][2]);
+      out.G[d][4] -= row_dot<PROD>(d, Sd, beta[0], beta[1], beta[2]);
     }
   }
 
   // spectral radii and their anisotropic scaling
   T lam[3];
-  for (int d = 0; d < 3; ++d) {
-    const T* Sd = in.S[d];
-    lam[d] = (tabs(Uc[d]) + a * tsqrt(Sd[0] * Sd[0] + Sd[1] * Sd[1] + Sd[2] * Sd[2])) * aiV;
-  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d) lam[d] = (tabs(Uc[d]) + a * row_norm<PROD>(d, in.S[d])) * aiV;
   // lambda_d + sqrt(lambda_d lambda_e) + sqrt(lambda_d lambda_f)
   //   = sqrt(lambda_d) (sqrt(lambda_d) + sqrt(lambda_e) + sqrt(lambda_f))
   const T r0 = tsqrt(lam[0]), r1 = tsqrt(lam[1]), r2 = tsqrt(lam[2]);
@@ -345,16 +397,15 @@ __host__ __device__ __forceinline__ void face_flux(const T GL[5], const T GR[5],
 
 // Sum of the spectral radii lambda_xi + lambda_eta + lambda_zeta at a point
 // (time-step restriction).
-template <typename T>
+template <bool PROD, typename T>
 __host__ __device__ __forceinline__ T lambda_sum(const T q[5], const T S[3][3], T V,
                                                  const Phys<T>& ph) {
   const Prim<T> s = primitives(q, ph);
   const T a = tsqrt(ph.gamma * s.p / s.rho);
   T tot = T(0);
-  for (int d = 0; d < 3; ++d) {
-    const T Uc = S[d][0] * s.u + S[d][1] * s.v + S[d][2] * s.w;
-    tot += tabs(Uc) + a * tsqrt(S[d][0] * S[d][0] + S[d][1] * S[d][1] + S[d][2] * S[d][2]);
-  }
+#pragma unroll
+  for (int d = 0; d < 3; ++d)
+    tot += tabs(row_dot<PROD>(d, S[d], s.u, s.v, s.w)) + a * row_norm<PROD>(d, S[d]);
   return tot / tabs(V);
 }
 

@@ -11,6 +11,6 @@ template hipError_t launch_fused<double>(const double*, const double*, const Gri
                                          const Phys<double>&, int, int, double*, const double*,
                                          double*, double, const double*, const Phys<double>&,
                                          unsigned long long*, int, double*, const double*,
-                                         hipStream_t);
+                                         const ProdTab&, hipStream_t);
 
 }  // namespace lesjet

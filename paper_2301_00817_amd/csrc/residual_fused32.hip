@@ -11,6 +11,7 @@ template int fused_chunk<float>(const Grid&, int);
 template hipError_t launch_fused<float>(const float*, const float*, const Grid&, const Phys<float>&,
                                         int, int, float*, const double*, double*, double,
                                         const double*, const Phys<double>&, unsigned long long*,
-                                        int, float*, const double*, hipStream_t);
+                                        int, float*, const double*,
+                                         const ProdTab&, hipStream_t);
 
 }  // namespace lesjet

@@ -10,9 +10,10 @@
 
 namespace lesjet {
 
-template <typename TQ, typename TM>
+template <typename TQ, typename TM, bool PROD>
 __global__ void k_lambda_max(const TQ* __restrict__ Q, const TM* __restrict__ M, Grid g,
-                             Phys<double> ph, unsigned long long* __restrict__ maxbits) {
+                             Phys<double> ph, ProdTab pt,
+                             unsigned long long* __restrict__ maxbits) {
   __shared__ double red[256];
   const long long tot = (long long)g.nx * g.nr * g.nth;
   double local = 0.0;
@@ -25,9 +26,19 @@ __global__ void k_lambda_max(const TQ* __restrict__ Q, const TM* __restrict__ M,
     const int o = g.at(i, j, k);
     double q[5], S[3][3];
     for (int c = 0; c < 5; ++c) q[c] = (double)Q[(long long)c * g.vs + o];
-    for (int d = 0; d < 3; ++d)
-      for (int c = 0; c < 3; ++c) S[d][c] = (double)M[(long long)(3 * d + c) * g.vs + o];
-    const double x = lambda_sum(q, S, (double)M[9LL * g.vs + o], ph);
+    double V;
+    if (PROD) {     // the stored terms are those of the storage type
+      double m[10];
+      product_terms(pt.x[i + NG], pt.yz + (long long)(k + NG) * prod_plane(g) + (j + NG) * 4, m);
+      for (int d = 0; d < 3; ++d)
+        for (int c = 0; c < 3; ++c) S[d][c] = (double)(TM)m[3 * d + c];
+      V = (double)(TM)m[9];
+    } else {
+      for (int d = 0; d < 3; ++d)
+        for (int c = 0; c < 3; ++c) S[d][c] = (double)M[(long long)(3 * d + c) * g.vs + o];
+      V = (double)M[9LL * g.vs + o];
+    }
+    const double x = lambda_sum<PROD>(q, S, V, ph);
     if (x != x || x > local) local = x;      // keeps a NaN once seen
   }
   red[threadIdx.x] = local;
@@ -94,12 +105,16 @@ __global__ void k_to_float(const double* __restrict__ a, float* __restrict__ b, 
 
 template <typename TQ, typename TM>
 hipError_t launch_lambda_max(const TQ* Q, const TM* M, const Grid& g, const Phys<double>& ph,
-                             unsigned long long* maxbits, hipStream_t s) {
+                             unsigned long long* maxbits, const ProdTab& pt, hipStream_t s) {
   const long long n = (long long)g.nx * g.nr * g.nth;
   long long b = (n + 255) / 256;
   if (b > 4096) b = 4096;
-  hipLaunchKernelGGL((k_lambda_max<TQ, TM>), dim3((unsigned)b), dim3(256), 0, s, Q, M, g, ph,
-                     maxbits);
+  if (pt.x)
+    hipLaunchKernelGGL((k_lambda_max<TQ, TM, true>), dim3((unsigned)b), dim3(256), 0, s, Q, M, g, ph,
+                       pt, maxbits);
+  else
+    hipLaunchKernelGGL((k_lambda_max<TQ, TM, false>), dim3((unsigned)b), dim3(256), 0, s, Q, M, g, ph,
+                       pt, maxbits);
   return hipGetLastError();
 }
 
@@ -133,10 +148,10 @@ hipError_t launch_to_float(const double* a, float* b, long long n, hipStream_t s
 
 template hipError_t launch_lambda_max<double, double>(const double*, const double*, const Grid&,
                                                       const Phys<double>&, unsigned long long*,
-                                                      hipStream_t);
+                                                      const ProdTab&, hipStream_t);
 template hipError_t launch_lambda_max<double, float>(const double*, const float*, const Grid&,
                                                      const Phys<double>&, unsigned long long*,
-                                                     hipStream_t);
+                                                     const ProdTab&, hipStream_t);
 template hipError_t launch_rk_update<double, double>(const double*, const double*, double*,
                                                      double*, const Grid&, double, const double*,
                                                      hipStream_t);
