@@ -8,11 +8,11 @@
 //       halo for the fourth differences) to LDS,
 //   (b) computes the point quantities G^d, lambda_bar^d, nu^d of every
 //       ring-1 column, with in-plane neighbours from LDS and the kk-1, kk+1
-//       neighbours from the thread's own registers, and publishes the xi and
-//       eta ones in LDS,
-//   (c) evaluates the in-plane faces i - 1/2 and j - 1/2 of each column from
-//       LDS and publishes their fluxes; after a barrier each interior column
-//       takes its flux differences from LDS and forms the zeta face kk-1/2
+//       neighbours from the thread's own registers, and publishes the eta
+//       ones in LDS (the xi ones go to the neighbouring lane),
+//   (c) evaluates the in-plane faces i - 1/2 and j - 1/2 of each column and
+//       publishes the eta fluxes; after a barrier each interior column
+//       takes its flux differences and forms the zeta face kk-1/2
 //       from registers (point quantities of plane kk-1 are kept from the
 //       previous iteration), which completes R at plane kk-1.
 // Every point quantity of a ring-1 column is computed once per plane, every
@@ -101,6 +101,34 @@ __device__ __forceinline__ void met_terms(const D m[], double xx, T out[]) {
   }
 }
 
+// Value of the lane one column to the left (right) in a tile row of X threads:
+// a data-parallel move within the wave (16-lane rows, or the whole wave where
+// a row is 32 lanes), executed with every lane active.  The first (last) lane
+// of a row gets zero or another row's value, which nothing uses.
+template <int CTRL>
+__device__ __forceinline__ int lane_mov(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_mov(float v) {
+  return __builtin_bit_cast(float, lane_mov<CTRL>(__builtin_bit_cast(int, v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double lane_mov(double v) {
+  const long long b = __builtin_bit_cast(long long, v);
+  const int lo = lane_mov<CTRL>((int)b), hi = lane_mov<CTRL>((int)(b >> 32));
+  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
+}
+template <int X, typename T>
+__device__ __forceinline__ T from_left(T v) {
+  static_assert(X == 16 || X == 32, "tile rows of 16 or 32 lanes");
+  return lane_mov<X == 16 ? 0x111 : 0x138>(v);      // row_shr:1, wave_shr:1
+}
+template <int X, typename T>
+__device__ __forceinline__ T from_right(T v) {
+  return lane_mov<X == 16 ? 0x101 : 0x130>(v);      // row_shl:1, wave_shl:1
+}
+
 // Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  The
 // hardware id is remapped so that XCD x receives a contiguous run of tiles,
 // i fastest, then j, then the k-chunk: tiles that share halos run at the
@@ -179,15 +207,20 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   constexpr int NBORDER = FR_X * FR_Y - FB_X * FB_Y;   // ring-2 points without a thread
   // plane state and primitives (one buffer: a second would save a barrier
   // per plane but costs a resident block per CU in either precision)
-  __shared__ T sQ[5][FR_Y][FR_X];
+  __shared__ T sQ[5][FR_Y][FR_X];     // W = (rho, rho u, rho v, rho w, E + p)
   __shared__ T sP[5][FR_Y][FR_X];
-  __shared__ T sX[NPQ][FB_Y][FB_X];
   __shared__ T sE[NPQ][FB_Y][FB_X];
   // fluxes of the faces i - 1/2 (xi) and j - 1/2 (eta) of each column: each
-  // in-plane face is evaluated once, by the column on its + side, and read
+  // in-plane face is evaluated once, by the column on its + side, and used
   // by both neighbours (evaluating it from both sides cost 11-14 % more time
-  // in FP64 and the registers of a fourth FP32 block per CU)
-  __shared__ T sFx[5][FB_Y][FB_X];
+  // in FP64 and the registers of a fourth FP32 block per CU).  Point
+  // quantities and fluxes cross the xi faces by lane moves, the eta faces
+  // through LDS: LDS was busy 45 % of the FP64 kernel's time when it carried
+  // both (and the thread's own values back to it), a moved double costs two
+  // vector moves on one of the four SIMDs against eight cycles of the CU's
+  // LDS.  102 M points: LDS 6.2 -> 3.5 M cycles per CU and launch, the stage
+  // 5.68 -> 5.21 ms; residual of a 95^3 mesh 74.0 -> 68.4 us, FP32 step on
+  // 23.6 M points 4.83 -> 4.54 ms.
   __shared__ T sFe[5][FB_Y][FB_X];
   __shared__ double sRed[(FB_X * FB_Y + 63) / 64];
 
@@ -236,7 +269,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   // The state and primitives of the current plane kk live in LDS once phase
   // (a) has written them; registers carry only what the march needs next.
   T Wa[5], Wb[5];        // W at kk-2, kk-1 (zeta fourth difference)
-  T Qd[5], Pd[5];        // Q and (u, v, w, T, p) at kk+1
+  T Qd[5], Pd[5];        // W and (u, v, w, T, p) at kk+1
   T Pb[5];               // (u, v, w, T, p) at kk-1
   T Qn[5];               // Q at kk+2, in flight
   using MD = MetData<T, PROD>;
@@ -279,11 +312,12 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     prim5(q, ph, pc);
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
-      sQ[c][ty + 1][tx + 1] = q[c];
+      sQ[c][ty + 1][tx + 1] = c == 4 ? radd(q[c], pc[c]) : q[c];
       sP[c][ty + 1][tx + 1] = pc[c];
     }
     load_q(Qin, g, oq, k0, Qd);
     prim5(Qd, ph, Pd);
+    Qd[4] = radd(Qd[4], Pd[4]);
     load_met<PROD>(M, ptab, g, oq, trow, k0 - 1, met);
     if (LAG == LAG_READ) load_lag(k0 - 1, lag);
   }
@@ -294,6 +328,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     T bq[5], bp[5];
     load_q(Qin, g, oob, k0 - 1, bq);
     prim5(bq, ph, bp);
+    bq[4] = radd(bq[4], bp[4]);
 #pragma unroll
     for (int c = 0; c < 5; ++c) {
       sQ[c][bry][brx] = bq[c];
@@ -346,7 +381,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       in.V = m[9];
     }
     if (LAG == LAG_READ) { in.mt = lag[0]; in.kap = lag[1]; }
-    point_quantities<T, LAG, DYN, PROD>(in, ph, po);
+    point_quantities<T, LAG, DYN, PROD, true>(in, ph, po);
     if (LAG == LAG_WRITE && col_ok && ph.viscous) {
       gst(visc, g, 0, kk, oq, po.mt);
       gst(visc, g, 1, kk, oq, po.kap);
@@ -358,13 +393,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       for (int c = 0; c < 5; ++c) po.G[1][c] = T(0);
     }
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      sX[c][ty][tx] = po.G[0][c];
-      sE[c][ty][tx] = po.G[1][c];
-    }
-    sX[5][ty][tx] = po.lb[0];
-    sX[6][ty][tx] = po.nu[0];
-    sX[7][ty][tx] = in.V;
+    for (int c = 0; c < 5; ++c) sE[c][ty][tx] = po.G[1][c];
     sE[5][ty][tx] = po.lb[1];
     sE[6][ty][tx] = po.nu[1];
     sE[7][ty][tx] = in.V;
@@ -376,57 +405,54 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
 
     // (c) faces
     if (WavePrio<T>::on) __builtin_amdgcn_s_setprio(1);
-    auto wload = [&](int yy, int xx, T w[5]) {      // W = Q with E replaced by E + p
+    auto wload = [&](int yy, int xx, T w[5]) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c) w[c] = sQ[c][yy][xx];
-      w[4] = sQ[4][yy][xx] + sP[4][yy][xx];
+      for (int c = 0; c < 5; ++c) w[c] = sQ[c][yy][xx];
     };
-    if (kk >= k0 && kk < k1) {
+    const T (&Wc)[5] = in.q;                        // W of the point itself
+    // flux differences of the in-plane faces (output planes only), the eta
+    // face j + 1/2 added after the barrier
+    T rhs[5] = {0, 0, 0, 0, 0}, Fe[5] = {0, 0, 0, 0, 0};
+    const bool planes = kk >= k0 && kk < k1;
+    if (planes) {
       // in-plane faces of the output planes, one per column and direction
-      T Wm[5], Wl[5], Wr[5], Wp[5], F[5], GA[5], GB[5];
+      T Wm[5], Wl[5], Wp[5], F[5] = {0, 0, 0, 0, 0}, GA[5];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) GA[c] = from_left<FB_X>(po.G[0][c]);
+      const T lbA = from_left<FB_X>(po.lb[0]), nuA = from_left<FB_X>(po.nu[0]),
+              VA = from_left<FB_X>(in.V);
       if (xface) {
-        wload(ty + 1, tx - 1, Wm); wload(ty + 1, tx, Wl); wload(ty + 1, tx + 1, Wr);
-        wload(ty + 1, tx + 2, Wp);
-#pragma unroll
-        for (int c = 0; c < 5; ++c) { GA[c] = sX[c][ty][tx - 1]; GB[c] = sX[c][ty][tx]; }
-        face_flux(GA, GB, sX[5][ty][tx - 1], sX[5][ty][tx], sX[6][ty][tx - 1], sX[6][ty][tx],
-                  sX[7][ty][tx - 1], sX[7][ty][tx], Wm, Wl, Wr, Wp, phys_xf, ph, F);
-#pragma unroll
-        for (int c = 0; c < 5; ++c) sFx[c][ty][tx] = F[c];
+        wload(ty + 1, tx - 1, Wm); wload(ty + 1, tx, Wl); wload(ty + 1, tx + 2, Wp);
+        face_flux(GA, po.G[0], lbA, po.lb[0], nuA, po.nu[0], VA, in.V, Wm, Wl, Wc, Wp, phys_xf, ph,
+                  F);
       }
+#pragma unroll
+      for (int c = 0; c < 5; ++c) rhs[c] = from_right<FB_X>(F[c]) - F[c];
       if (eface) {
         // axis face: lambda_bar of row 1 and the three-point fourth
         // difference W(2) - 4 W(1) + 3 W(0), i.e. the standard formula with
         // W(-1) replaced by W(1); done by choosing the rows read
         const int rm = AXIS && axis_face ? ty + 1 : ty - 1;
-        const int rl = AXIS && axis_face ? ty : ty - 1;
-        wload(rm, tx + 1, Wm); wload(ty, tx + 1, Wl); wload(ty + 1, tx + 1, Wr);
-        wload(ty + 2, tx + 1, Wp);
+        wload(rm, tx + 1, Wm); wload(ty, tx + 1, Wl); wload(ty + 2, tx + 1, Wp);
 #pragma unroll
-        for (int c = 0; c < 5; ++c) { GA[c] = sE[c][ty - 1][tx]; GB[c] = sE[c][ty][tx]; }
-        face_flux(GA, GB, sE[5][rl][tx], sE[5][ty][tx], sE[6][ty - 1][tx], sE[6][ty][tx],
-                  sE[7][ty - 1][tx], sE[7][ty][tx], Wm, Wl, Wr, Wp, phys_ef, ph, F);
+        for (int c = 0; c < 5; ++c) GA[c] = sE[c][ty - 1][tx];
+        const T lbE = AXIS && axis_face ? po.lb[1] : sE[5][ty - 1][tx];
+        face_flux(GA, po.G[1], lbE, po.lb[1], sE[6][ty - 1][tx], po.nu[1], sE[7][ty - 1][tx], in.V,
+                  Wm, Wl, Wc, Wp, phys_ef, ph, Fe);
 #pragma unroll
-        for (int c = 0; c < 5; ++c) sFe[c][ty][tx] = F[c];
+        for (int c = 0; c < 5; ++c) sFe[c][ty][tx] = Fe[c];
       }
     }
     __syncthreads();
     if (interior && kk >= k0) {
       const bool emit = kk - 1 >= k0;       // R at (i, j, kk-1) completes here
-      // flux differences of the in-plane faces (output planes only)
-      T rhs[5] = {0, 0, 0, 0, 0};
-      if (kk < k1) {
+      if (planes) {
 #pragma unroll
-        for (int c = 0; c < 5; ++c)
-          rhs[c] = sFx[c][ty][tx + 1] - sFx[c][ty][tx] + sFe[c][ty + 1][tx] - sFe[c][ty][tx];
+        for (int c = 0; c < 5; ++c) rhs[c] = rhs[c] + sFe[c][ty + 1][tx] - Fe[c];
       }
       // zeta face kk-1/2: L = kk-1 (registers), R = kk
-      T Wc[5], Wd[5], Fk[5];
-#pragma unroll
-      for (int c = 0; c < 5; ++c) { Wc[c] = sQ[c][ty + 1][tx + 1]; Wd[c] = Qd[c]; }
-      Wc[4] += sP[4][ty + 1][tx + 1];
-      Wd[4] += Pd[4];
-      face_flux(Gz, po.G[2], lbz, po.lb[2], nuz, po.nu[2], Vz, in.V, Wa, Wb, Wc, Wd, false, ph, Fk);
+      T Fk[5];
+      face_flux(Gz, po.G[2], lbz, po.lb[2], nuz, po.nu[2], Vz, in.V, Wa, Wb, Wc, Qd, false, ph, Fk);
       if (emit) {
         // the epilogue's loads ahead of its stores (the compiler cannot order
         // buffer accesses of different arrays by itself): Q^(0) of the output
@@ -477,10 +503,9 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     for (int c = 0; c < 5; ++c) {
       Gz[c] = po.G[2][c];
       Wa[c] = Wb[c];
-      Wb[c] = sQ[c][ty + 1][tx + 1];     // own state of plane kk, re-read from LDS
-      Pb[c] = sP[c][ty + 1][tx + 1];
+      Wb[c] = Wc[c];
+      Pb[c] = sP[c][ty + 1][tx + 1];     // re-read from LDS
     }
-    Wb[4] += Pb[4];
     lbz = po.lb[2];
     nuz = po.nu[2];
     Vz = in.V;
@@ -499,6 +524,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
         if (DEFER) load_q(Qin, g, oob, kk + 1, Bn);
         T bp[5];
         prim5(Bn, ph, bp);
+        Bn[4] = radd(Bn[4], bp[4]);
 #pragma unroll
         for (int c = 0; c < 5; ++c) {
           sQ[c][bry][brx] = Bn[c];
@@ -506,6 +532,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
         }
       }
       prim5(Qd, ph, Pd);
+      Qd[4] = radd(Qd[4], Pd[4]);
       if (CS) {
 #pragma unroll
         for (int c = 0; c < MD::NS; ++c) Sp[c] = met[c];

@@ -152,6 +152,12 @@ __host__ __device__ __forceinline__ T rmul(T a, T b) {
 #pragma clang fp contract(off)
   return a * b;
 }
+// A sum in which no product is contracted.
+template <typename T>
+__host__ __device__ __forceinline__ T radd(T a, T b) {
+#pragma clang fp contract(off)
+  return a + b;
+}
 
 // Metric terms m[0..9] (S^xi, S^eta, S^zeta, J^-1) of a product mesh point from
 // x_xi and t = (y_eta, z_eta, y_zeta, z_zeta): the central-difference formulas of
@@ -247,8 +253,8 @@ enum { LAG_NONE = 0, LAG_WRITE = 1, LAG_READ = 2 };
 // DYN: the dynamic SGS model's terms are compiled in (used when ph.sgs == 3);
 // a separate instance so that the other models carry none of them.
 // PROD: product mesh (the zero metric terms are not touched); separate for
-// the same reason.
-template <typename T, int LAG = LAG_NONE, bool DYN = false, bool PROD = false>
+// the same reason.  ENTH: in.q[4] holds E + p instead of E.
+template <typename T, int LAG = LAG_NONE, bool DYN = false, bool PROD = false, bool ENTH = false>
 __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phys<T>& ph,
                                                  PointOut<T>& out) {
   Prim<T> s;
@@ -271,7 +277,7 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
       if (PROD && (d == 0) != (m == 0)) out.G[d][1 + m] = rmul(in.q[1 + m], Uc[d]);
       else out.G[d][1 + m] = in.q[1 + m] * Uc[d] + s.p * in.S[d][m];
     }
-    out.G[d][4] = (in.q[4] + s.p) * Uc[d];
+    out.G[d][4] = (ENTH ? in.q[4] : in.q[4] + s.p) * Uc[d];
   }
 
   if (ph.viscous) {
