@@ -129,6 +129,17 @@ __device__ __forceinline__ T from_right(T v) {
   return lane_mov<X == 16 ? 0x101 : 0x130>(v);      // row_shl:1, wave_shl:1
 }
 
+// s_waitcnt operand: no vector memory access outstanding (LDS and scalar
+// counters not waited for).  The compiler places its waits for the fewest
+// accesses issued on any path; the loads of the march sit in branches, so a
+// wait of its own for an older load also drains every newer one.  Waiting
+// where nothing young is in flight (before the march, and ahead of the
+// epilogue's stores) clears its record: the loads at the top of an iteration
+// then stay in flight through the point phase, and no load is waited for
+// behind a store.  8 % of the FP64 step with held viscosities on 1.0 M points,
+// 3-4 % of the steps on 102 M (FP64) and 23.6 M points (FP32).
+constexpr int WAIT_VMEM = 0x0F70;
+
 // Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  The
 // hardware id is remapped so that XCD x receives a contiguous run of tiles,
 // i fastest, then j, then the k-chunk: tiles that share halos run at the
@@ -278,10 +289,11 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   constexpr bool CS = EPI == EPI_RK_LAST;        // metric terms carried (above)
   constexpr bool DEFER = CS && sizeof(T) == 8;    // loads deferred to free registers
   constexpr bool PQ0 = EPI != EPI_R && !CS && PrefetchQ0<T>::on;
-  // the own column two planes ahead is loaded at the top of the iteration
-  // in FP64 stages 1-4, after the point phase elsewhere (measured: the FP64
-  // last stage 2 % and FP32 stages 1 % faster, FP64 stages 1-4 4 % slower)
-  constexpr bool LATE_QN = sizeof(T) == 4 || CS;
+  // the own column two planes ahead is loaded after the point phase in FP64
+  // (2-4 % faster than at the top of the iteration; with held viscosities
+  // 2 % slower) and on general FP32 meshes, at the top otherwise (FP32
+  // product meshes: 2 % faster)
+  constexpr bool LATE_QN = sizeof(T) == 8 ? LAG == LAG_NONE || CS : !PROD;
   double q0p[5];         // Q^(0) at (i, j, kk-1), loaded at the top of iteration kk
   const double ad_pre = PQ0 ? alpha * (*dtp) : 0.0;
   auto load_lag = [&](int kk, T v[2]) {
@@ -336,6 +348,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     }
   }
 
+  __builtin_amdgcn_s_waitcnt(WAIT_VMEM);
   for (int kk = k0 - 1; kk <= k1; ++kk) {
     const bool more = kk < k1;
     // metric loads of the next plane (and, early, the own column two planes
@@ -444,6 +457,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       }
     }
     __syncthreads();
+    __builtin_amdgcn_s_waitcnt(WAIT_VMEM);
     if (interior && kk >= k0) {
       const bool emit = kk - 1 >= k0;       // R at (i, j, kk-1) completes here
       if (planes) {
