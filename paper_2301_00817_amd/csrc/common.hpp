@@ -61,14 +61,19 @@ struct Vec5 { T v[5]; };
 // Metric tables of a product mesh: x depends on i alone, y and z on (j, k)
 // alone (cylindrical jet meshes, Cartesian boxes), so that all ten metric
 // terms of a point follow from x_xi(i) and (y_eta, z_eta, y_zeta, z_zeta)(j, k)
-// (product_terms in physics.hpp).  FP64 in both precision forms.  x == NULL:
-// not a product mesh, the stored metric arrays are read instead.
+// (product_terms in physics.hpp), and with A = S^xi / 1 the area of the (j, k)
+// cell, J^-1 = x_xi A, so do its reciprocal, the lengths of the area vectors
+// and the filter width.  FP64 in both precision forms.  x == NULL: not a
+// product mesh, the stored metric arrays are read instead.
+constexpr int PX_N = 4;         // x_xi, 1 / x_xi, |x_xi|^(2/3), unused
+constexpr int PT_N = 8;         // y_eta, z_eta, y_zeta, z_zeta, |S^eta| / x_xi,
+                                // |S^zeta| / x_xi, 1 / A, |A|^(2/3)
 struct ProdTab {
-  const double* x = nullptr;    // [nx + 4]
-  const double* yz = nullptr;   // [nth + 4][nr + 4][4]
+  const double* x = nullptr;    // [nx + 4][PX_N]
+  const double* yz = nullptr;   // [nth + 4][nr + 4][PT_N]
 };
 // The (j, k) table's stride between planes, in doubles.
-__host__ __device__ __forceinline__ int prod_plane(const Grid& g) { return (g.nr + 2 * NG) * 4; }
+__host__ __device__ __forceinline__ int prod_plane(const Grid& g) { return (g.nr + 2 * NG) * PT_N; }
 
 // Sizes of the state arrays a kernel touches, per launch.
 inline unsigned blocks_for(long long n, int bs) { return (unsigned)((n + bs - 1) / bs); }

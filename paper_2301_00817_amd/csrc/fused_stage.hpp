@@ -68,39 +68,6 @@ __device__ __forceinline__ void load_metrics(const T* M, const Grid& g, unsigned
   for (int c = 0; c < 10; ++c) m[c] = gld(M, g, c, k, col);
 }
 
-// Metric data of a column along the march: the ten stored terms of a plane,
-// or (product mesh) the plane's four (j, k) table values, expanded to the
-// terms where used.  col, row: the column's offset within a plane of the
-// metric arrays (bytes) and of the table (elements).
-template <typename T, bool PROD> struct MetData { using type = T; static constexpr int N = 10, NS = 9; };
-template <typename T> struct MetData<T, true> { using type = double; static constexpr int N = 4, NS = 4; };
-
-template <bool PROD, typename T, typename D>
-__device__ __forceinline__ void load_met(const T* M, const ProdTab& pt, const Grid& g, unsigned col,
-                                         int row, int k, D m[]) {
-  if constexpr (PROD) {
-    const double* p = pt.yz + (long long)(k + NG) * prod_plane(g);
-#pragma unroll
-    for (int c = 0; c < 4; ++c) m[c] = p[row + c];
-  } else {
-    load_metrics(M, g, col, k, m);
-  }
-}
-
-// n = 10, or 9 without J^-1
-template <bool PROD, int n, typename T, typename D>
-__device__ __forceinline__ void met_terms(const D m[], double xx, T out[]) {
-  if constexpr (PROD) {
-    double w[10];
-    product_terms(xx, m, w);
-#pragma unroll
-    for (int c = 0; c < n; ++c) out[c] = (T)w[c];
-  } else {
-#pragma unroll
-    for (int c = 0; c < n; ++c) out[c] = m[c];
-  }
-}
-
 // Value of the lane one column to the left (right) in a tile row of X threads:
 // a data-parallel move within the wave (16-lane rows, or the whole wave where
 // a row is 32 lanes), executed with every lane active.  The first (last) lane
@@ -159,10 +126,11 @@ template <typename T> struct PrefetchQ0 { static constexpr bool on = sizeof(T) =
 // The last stage of a step evaluates the next step's CFL sum at its output
 // point, which needs that point's metric terms, loaded two planes earlier
 // and no longer in L2 (reloading them cost the FP64 kernel 10 ms, a sixth
-// of the stage, on 1e9 points).  The stage carries them from the previous
-// plane in registers instead: FP64 frees the registers by loading Q^(0) and
-// the next plane's border where they are used rather than ahead; FP32 runs
-// that stage at three waves per SIMD (at four it spills).
+// of the stage, on 1e9 points).  On a product mesh they come from the table
+// rows in LDS; else the stage carries them from the previous plane in
+// registers: FP64 frees the registers by loading Q^(0) and the next plane's
+// border where they are used rather than ahead; FP32 runs that stage at three
+// waves per SIMD (at four it spills; product meshes fit four, 1 % faster).
 
 // Wave priority: the FP64 kernel (two waves per SIMD, bound by latency)
 // raises its waves' issue priority from the face phase to the end of the
@@ -175,12 +143,12 @@ template <typename T> struct PrefetchQ0 { static constexpr bool on = sizeof(T) =
 template <typename T> struct WavePrio { static constexpr bool on = sizeof(T) == 8; };
 
 // Register budget: FP64 two waves per SIMD (up to 256 VGPRs), FP32 four
-// (128), three (168) in the last stage.
+// (128), three (168) in the last stage of general meshes.
 template <typename T> struct FusedOcc;
 template <> struct FusedOcc<double> { static constexpr int waves = 2; };
 template <> struct FusedOcc<float> { static constexpr int waves = 4; };
-template <typename T, int EPI> struct FusedOccE { static constexpr int waves = FusedOcc<T>::waves; };
-template <> struct FusedOccE<float, EPI_RK_LAST> { static constexpr int waves = 3; };
+template <typename T, int EPI, bool PROD> struct FusedOccE { static constexpr int waves = FusedOcc<T>::waves; };
+template <> struct FusedOccE<float, EPI_RK_LAST, false> { static constexpr int waves = 3; };
 
 // AXIS: the eta- face is a centerline through mesh nodes (row j = 0 on the
 // axis); a separate instance so that the common case carries none of it.
@@ -189,16 +157,20 @@ template <> struct FusedOccE<float, EPI_RK_LAST> { static constexpr int waves = 
 // padded variables; LAG_READ takes them from there).  The tiling is the same
 // in every stage, so the points read are those written; points shared by
 // two blocks are written twice with the same value.
-// PROD: product mesh.  The ten metric terms are formed from tables (four
-// FP64 values per (j, k), read once per plane by each row, one per i), which
-// spares 80 of the 200 bytes per point and stage (FP32: 40 of 128), the
-// registers of two planes of metric terms, and the arithmetic on the four
-// terms that are zero.  The terms and results are bitwise those of the general
-// form in FP64.  A step (with the first reduction of dt, which reads the same
+// PROD: product mesh.  The ten metric terms, the reciprocal of J^-1, the lengths
+// of the area vectors and the filter width are formed from tables (eight FP64
+// values per (j, k), staged in LDS once per plane and tile row by threads that
+// hold no border point, three per i), which spares 80 of the 200 bytes per
+// point and stage (FP32: 40 of 128), the registers of two planes of metric
+// terms, and the arithmetic on the four terms that are zero.  The terms and results are bitwise those of the general
+// form in FP64 (the derived values within two ulps).  A step (with the first reduction of dt, which reads the same
 // tables): 36.7 -> 28.4 ms on 102 M points, 4.21 -> 3.61 ms for two on 5.9 M,
-// FP32 5.77 -> 4.83 ms on 23.6 M.
+// FP32 5.77 -> 4.83 ms on 23.6 M.  The derived values (FP64 only: the FP32
+// hardware reciprocal, root and logarithm cost no more than the products)
+// spare a reciprocal, two roots and a cube root of the 850 vector operations
+// per point and plane: another 3 % (24.0 -> 23.1 ms on 102 M points).
 template <typename T, int EPI, bool AXIS, int LAG, bool DYN, bool PROD>
-__global__ void __launch_bounds__(Tile<T>::X * Tile<T>::Y, (FusedOccE<T, EPI>::waves))
+__global__ void __launch_bounds__(Tile<T>::X * Tile<T>::Y, (FusedOccE<T, EPI, PROD>::waves))
 k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_arg, int kc,
         TileMap tm, T* out, const double* Q0, double* Q64, double alpha,
         const double* __restrict__ dtp, Phys<double> ph64, unsigned long long* __restrict__ maxbits,
@@ -234,6 +206,8 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   // 23.6 M points 4.83 -> 4.54 ms.
   __shared__ T sFe[5][FB_Y][FB_X];
   __shared__ double sRed[(FB_X * FB_Y + 63) / 64];
+  // product mesh: table rows of the planes kk-1 .. kk+1 (slot = plane mod 4)
+  __shared__ __align__(16) double sM[PROD ? 4 : 1][FB_Y][PT_N];
 
   const int tx = threadIdx.x, ty = threadIdx.y;
   const int tid = ty * FB_X + tx;
@@ -283,8 +257,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   T Qd[5], Pd[5];        // W and (u, v, w, T, p) at kk+1
   T Pb[5];               // (u, v, w, T, p) at kk-1
   T Qn[5];               // Q at kk+2, in flight
-  using MD = MetData<T, PROD>;
-  typename MD::type met[MD::N], metn[MD::N];   // metrics at (i, j, kk), prefetch for kk+1
+  T met[10], metn[10];   // general mesh: metrics at (i, j, kk), prefetch for kk+1
   T lag[2], lagn[2];     // held (mu + mu_sgs, conductivity), same planes (LAG_READ)
   constexpr bool CS = EPI == EPI_RK_LAST;        // metric terms carried (above)
   constexpr bool DEFER = CS && sizeof(T) == 8;    // loads deferred to free registers
@@ -303,15 +276,28 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     v[1] = gld(visc, g, 1, kk, oq);
   };
   // zeta-face state of plane kk-1 (interior columns)
-  T Gz[5], lbz = 0, nuz = 0, Vz = 0;
-  T acc[5];              // RHS at kk-1 without its zeta face kk-1/2:
+  T Gz[5], lbz = 0, nuz = 0, Vz = 0, hiVz = 0;   // hiVz = 1 / (2 Vz)
+  T acc[5];              // twice the RHS at kk-1 without its zeta face kk-1/2:
                          // in-plane faces minus the zeta face kk-3/2
   double lmax = 0.0;
-  typename MD::type Sp[MD::NS];   // last stage: metric terms of plane kk-1
-  // product mesh: x_xi of the column, its row of the (j, k) table (columns
-  // beyond the padded box take the nearest point's, as for the state)
-  const double xx = PROD ? ptab.x[min(max(i, -NG), g.nx + NG - 1) + NG] : 0.0;
-  const int trow = (min(max(j, -NG), g.nr + NG - 1) + NG) * 4;
+  T Sp[9];               // the same, last stage: metric terms of plane kk-1
+  // product mesh: the column's values of the x table; the table value this
+  // thread stages (columns and rows beyond the padded box take the nearest
+  // point's, as for the state)
+  constexpr int TAB0 = 128;
+  static_assert(NBORDER <= TAB0 && TAB0 + FB_Y * PT_N <= FB_X * FB_Y, "threads of the table rows");
+  double xx = 0, rx = 0, d2x = 0, mt = 0;
+  const int tr = (tid - TAB0) / PT_N, tc = (tid - TAB0) % PT_N;
+  const bool has_t = PROD && tid >= TAB0 && tr < FB_Y;
+  const int trow = (min(max(j0 - 1 + tr, -NG), g.nr + NG - 1) + NG) * PT_N + tc;
+  auto tab = [&](int k) { return ptab.yz[(long long)(k + NG) * prod_plane(g) + trow]; };
+  if (PROD) {
+    const double* px = ptab.x + (min(max(i, -NG), g.nx + NG - 1) + NG) * PX_N;
+    xx = px[0];
+    rx = px[1];
+    d2x = px[2];
+    if (has_t) sM[0][tr][tc] = tab(k0 - 1);
+  }
 
   {
     T q[5], pc[5];
@@ -330,7 +316,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     load_q(Qin, g, oq, k0, Qd);
     prim5(Qd, ph, Pd);
     Qd[4] = radd(Qd[4], Pd[4]);
-    load_met<PROD>(M, ptab, g, oq, trow, k0 - 1, met);
+    if (!PROD) load_metrics(M, g, oq, k0 - 1, met);
     if (LAG == LAG_READ) load_lag(k0 - 1, lag);
   }
 #pragma unroll
@@ -349,13 +335,14 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   }
 
   __builtin_amdgcn_s_waitcnt(WAIT_VMEM);
-  for (int kk = k0 - 1; kk <= k1; ++kk) {
+  for (int kk = k0 - 1, slot = 0; kk <= k1; ++kk, slot = (slot + 1) & 3) {
     const bool more = kk < k1;
     // metric loads of the next plane (and, early, the own column two planes
     // ahead), in flight during (b)
     if (more) {
       if (!LATE_QN && kk + 2 <= k1 + 1) load_q(Qin, g, oq, kk + 2, Qn);
-      load_met<PROD>(M, ptab, g, oq, trow, kk + 1, metn);
+      if (!PROD) load_metrics(M, g, oq, kk + 1, metn);
+      else if (has_t) mt = tab(kk + 1);
       if (LAG == LAG_READ) load_lag(kk + 1, lagn);
     }
     if (PQ0 && interior && kk - 1 >= k0) {
@@ -378,15 +365,31 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       T m[5], pl[5];
 #pragma unroll
       for (int f = 0; f < 5; ++f) { m[f] = sP[f][ty + 1][tx]; pl[f] = sP[f][ty + 1][tx + 2]; }
-      neighbour_terms(m, pl, in.pr[4], in.dl[0], in.nu[0]);
+      neighbour_terms<true>(m, pl, in.pr[4], in.dl[0], in.nu[0]);
 #pragma unroll
       for (int f = 0; f < 5; ++f) { m[f] = sP[f][ty][tx + 1]; pl[f] = sP[f][ty + 2][tx + 1]; }
-      neighbour_terms(m, pl, in.pr[4], in.dl[1], in.nu[1]);
-      neighbour_terms(Pb, Pd, in.pr[4], in.dl[2], in.nu[2]);
+      neighbour_terms<true>(m, pl, in.pr[4], in.dl[1], in.nu[1]);
+      neighbour_terms<true>(Pb, Pd, in.pr[4], in.dl[2], in.nu[2]);
     }
     {
       T m[10];
-      met_terms<PROD, 10>(met, xx, m);
+      if constexpr (PROD) {
+        double w[10];
+        const double* t = sM[slot][ty];
+        product_terms(xx, t, w);
+#pragma unroll
+        for (int c = 0; c < 10; ++c) m[c] = (T)w[c];
+        if (sizeof(T) == 8) {      // in FP32 the hardware functions cost no more
+          in.iV = rx * t[6];
+          in.len[0] = tabs(m[0]);
+          in.len[1] = fabs(xx) * t[4];
+          in.len[2] = fabs(xx) * t[5];
+          in.d2 = d2x * t[7];
+        }
+      } else {
+#pragma unroll
+        for (int c = 0; c < 10; ++c) m[c] = met[c];
+      }
 #pragma unroll
       for (int d = 0; d < 3; ++d)
 #pragma unroll
@@ -423,21 +426,25 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       for (int c = 0; c < 5; ++c) w[c] = sQ[c][yy][xx];
     };
     const T (&Wc)[5] = in.q;                        // W of the point itself
-    // flux differences of the in-plane faces (output planes only), the eta
-    // face j + 1/2 added after the barrier
-    T rhs[5] = {0, 0, 0, 0, 0}, Fe[5] = {0, 0, 0, 0, 0};
+    // In-plane faces of the output planes, one per column and direction.
+    // Threads without a face keep values that no output uses: the point
+    // fluxes, whose registers the face fluxes take over (zeros would be
+    // moved in for every plane).  rhs: flux differences (of doubled fluxes),
+    // the eta face j + 1/2 added after the barrier.
+    T rhs[5], Fe[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) { rhs[c] = po.G[0][c]; Fe[c] = po.G[1][c]; }
     const bool planes = kk >= k0 && kk < k1;
     if (planes) {
-      // in-plane faces of the output planes, one per column and direction
-      T Wm[5], Wl[5], Wp[5], F[5] = {0, 0, 0, 0, 0}, GA[5];
+      T Wm[5], Wl[5], Wp[5], GA[5], (&F)[5] = rhs;
 #pragma unroll
       for (int c = 0; c < 5; ++c) GA[c] = from_left<FB_X>(po.G[0][c]);
       const T lbA = from_left<FB_X>(po.lb[0]), nuA = from_left<FB_X>(po.nu[0]),
               VA = from_left<FB_X>(in.V);
       if (xface) {
         wload(ty + 1, tx - 1, Wm); wload(ty + 1, tx, Wl); wload(ty + 1, tx + 2, Wp);
-        face_flux(GA, po.G[0], lbA, po.lb[0], nuA, po.nu[0], VA, in.V, Wm, Wl, Wc, Wp, phys_xf, ph,
-                  F);
+        face_flux2(GA, po.G[0], lbA, po.lb[0], nuA, po.nu[0], VA, in.V, Wm, Wl, Wc, Wp, phys_xf, ph,
+                   F);
       }
 #pragma unroll
       for (int c = 0; c < 5; ++c) rhs[c] = from_right<FB_X>(F[c]) - F[c];
@@ -450,8 +457,8 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
 #pragma unroll
         for (int c = 0; c < 5; ++c) GA[c] = sE[c][ty - 1][tx];
         const T lbE = AXIS && axis_face ? po.lb[1] : sE[5][ty - 1][tx];
-        face_flux(GA, po.G[1], lbE, po.lb[1], sE[6][ty - 1][tx], po.nu[1], sE[7][ty - 1][tx], in.V,
-                  Wm, Wl, Wc, Wp, phys_ef, ph, Fe);
+        face_flux2(GA, po.G[1], lbE, po.lb[1], sE[6][ty - 1][tx], po.nu[1], sE[7][ty - 1][tx], in.V,
+                   Wm, Wl, Wc, Wp, phys_ef, ph, Fe);
 #pragma unroll
         for (int c = 0; c < 5; ++c) sFe[c][ty][tx] = Fe[c];
       }
@@ -460,13 +467,9 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     __builtin_amdgcn_s_waitcnt(WAIT_VMEM);
     if (interior && kk >= k0) {
       const bool emit = kk - 1 >= k0;       // R at (i, j, kk-1) completes here
-      if (planes) {
-#pragma unroll
-        for (int c = 0; c < 5; ++c) rhs[c] = rhs[c] + sFe[c][ty + 1][tx] - Fe[c];
-      }
       // zeta face kk-1/2: L = kk-1 (registers), R = kk
       T Fk[5];
-      face_flux(Gz, po.G[2], lbz, po.lb[2], nuz, po.nu[2], Vz, in.V, Wa, Wb, Wc, Qd, false, ph, Fk);
+      face_flux2(Gz, po.G[2], lbz, po.lb[2], nuz, po.nu[2], Vz, in.V, Wa, Wb, Wc, Qd, false, ph, Fk);
       if (emit) {
         // the epilogue's loads ahead of its stores (the compiler cannot order
         // buffer accesses of different arrays by itself): Q^(0) of the output
@@ -479,17 +482,19 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
           for (int c = 0; c < 5; ++c) q0[c] = PQ0 ? q0p[c] : gld(Q0, g, c, kk - 1, oq64);
         }
         if (EPI == EPI_RK_LAST) {
-          T m[9];
-          met_terms<PROD, 9>(Sp, xx, m);
+          double w[10];
+          if constexpr (PROD) product_terms(xx, sM[(slot + 3) & 3][ty], w);
 #pragma unroll
           for (int d = 0; d < 3; ++d)
 #pragma unroll
-            for (int c = 0; c < 3; ++c) S[d][c] = (double)m[3 * d + c];
+            for (int c = 0; c < 3; ++c)
+              S[d][c] = PROD ? (double)(T)w[3 * d + c] : (double)Sp[3 * d + c];
         }
-        const T iV = trcp(Vz);
+        // (general FP64 instances have no registers left to carry it)
+        const T hiV = PROD || sizeof(T) == 4 ? hiVz : T(0.5) * trcp(Vz);
         T R[5];
 #pragma unroll
-        for (int c = 0; c < 5; ++c) R[c] = AXIS && axis_row ? T(0) : (acc[c] + Fk[c]) * iV;
+        for (int c = 0; c < 5; ++c) R[c] = AXIS && axis_row ? T(0) : (acc[c] + Fk[c]) * hiV;
         if (EPI == EPI_R) {
 #pragma unroll
           for (int c = 0; c < 5; ++c) gst(out, g, c, kk - 1, oq, R[c]);
@@ -508,8 +513,10 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
           }
         }
       }
+      if (planes) {
 #pragma unroll
-      for (int c = 0; c < 5; ++c) acc[c] = rhs[c] - Fk[c];
+        for (int c = 0; c < 5; ++c) acc[c] = rhs[c] + sFe[c][ty + 1][tx] - Fe[c] - Fk[c];
+      }
     }
     if (WavePrio<T>::on) __builtin_amdgcn_s_setprio(0);
     // keep the zeta-direction point quantities of plane kk, roll the window
@@ -523,6 +530,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     lbz = po.lb[2];
     nuz = po.nu[2];
     Vz = in.V;
+    hiVz = po.hiV;
     // plane kk is read by other threads until the barrier after the face
     // fluxes; what follows reads only the thread's own column, which the
     // next plane's border writes never touch
@@ -547,12 +555,16 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
       }
       prim5(Qd, ph, Pd);
       Qd[4] = radd(Qd[4], Pd[4]);
-      if (CS) {
+      if (PROD) {
+        if (has_t) sM[(slot + 1) & 3][tr][tc] = mt;
+      } else {
+        if (CS) {
 #pragma unroll
-        for (int c = 0; c < MD::NS; ++c) Sp[c] = met[c];
+          for (int c = 0; c < 9; ++c) Sp[c] = met[c];
+        }
+#pragma unroll
+        for (int c = 0; c < 10; ++c) met[c] = metn[c];
       }
-#pragma unroll
-      for (int c = 0; c < MD::N; ++c) met[c] = metn[c];
       if (LAG == LAG_READ) { lag[0] = lagn[0]; lag[1] = lagn[1]; }
     }
   }

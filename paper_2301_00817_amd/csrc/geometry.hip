@@ -91,13 +91,24 @@ __global__ void k_prod_tab(const double* __restrict__ C, CGrid cg, Grid g, doubl
     const int j = t % NR - NG, k = t / NR - NG;
     const double* Y = C + (long long)cg.vs;
     const double* Z = C + 2LL * cg.vs;
-    yz[4 * t + 0] = 0.5 * (Y[cg.at(0, j + 1, k)] - Y[cg.at(0, j - 1, k)]);
-    yz[4 * t + 1] = 0.5 * (Z[cg.at(0, j + 1, k)] - Z[cg.at(0, j - 1, k)]);
-    yz[4 * t + 2] = 0.5 * (Y[cg.at(0, j, k + 1)] - Y[cg.at(0, j, k - 1)]);
-    yz[4 * t + 3] = 0.5 * (Z[cg.at(0, j, k + 1)] - Z[cg.at(0, j, k - 1)]);
+    double* o = yz + (long long)PT_N * t;
+    o[0] = 0.5 * (Y[cg.at(0, j + 1, k)] - Y[cg.at(0, j - 1, k)]);
+    o[1] = 0.5 * (Z[cg.at(0, j + 1, k)] - Z[cg.at(0, j - 1, k)]);
+    o[2] = 0.5 * (Y[cg.at(0, j, k + 1)] - Y[cg.at(0, j, k - 1)]);
+    o[3] = 0.5 * (Z[cg.at(0, j, k + 1)] - Z[cg.at(0, j, k - 1)]);
+    const double A = o[0] * o[3] - o[2] * o[1], cA = cbrt(fabs(A));
+    o[4] = sqrt(o[2] * o[2] + o[3] * o[3]);
+    o[5] = sqrt(o[0] * o[0] + o[1] * o[1]);
+    o[6] = 1.0 / A;
+    o[7] = cA * cA;
   } else if (t < n + NX) {
     const int i = t - n - NG;
-    x[t - n] = 0.5 * (C[cg.at(i + 1, 0, 0)] - C[cg.at(i - 1, 0, 0)]);
+    const double xx = 0.5 * (C[cg.at(i + 1, 0, 0)] - C[cg.at(i - 1, 0, 0)]), cx = cbrt(fabs(xx));
+    double* o = x + (long long)PX_N * (t - n);
+    o[0] = xx;
+    o[1] = 1.0 / xx;
+    o[2] = cx * cx;
+    o[3] = 0.0;
   }
 }
 
@@ -142,7 +153,8 @@ __global__ void k_metrics(const double* __restrict__ C, CGrid cg, T* __restrict_
     if (M64)
       for (int c = 0; c < 10; ++c) M64[(long long)c * g.vs + o] = m[c];
     double mp[10];
-    product_terms(pt.x[i + NG], pt.yz + (long long)(k + NG) * prod_plane(g) + (j + NG) * 4, mp);
+    product_terms(pt.x[(i + NG) * PX_N],
+                  pt.yz + (long long)(k + NG) * prod_plane(g) + (j + NG) * PT_N, mp);
     for (int c = 0; c < 10; ++c) same = same && (T)m[c] == (T)mp[c];
   }
   if (!same) *general = 1;

@@ -19,7 +19,7 @@ template <typename T>
 hipError_t launch_metrics(const double* C, const CGrid& cg, T* M, const Grid& g, double* M64,
                           double* tab, int* general, hipStream_t s);
 inline size_t prod_tab_doubles(const Grid& g) {
-  return (size_t)(g.nth + 2 * NG) * prod_plane(g) + (size_t)(g.nx + 2 * NG);
+  return (size_t)(g.nth + 2 * NG) * prod_plane(g) + (size_t)(g.nx + 2 * NG) * PX_N;
 }
 inline ProdTab prod_tab(const double* tab, const Grid& g) {
   ProdTab pt;

@@ -27,8 +27,10 @@ namespace lesjet {
 
 #if defined(__HIP_DEVICE_COMPILE__) && !defined(LESJET_IEEE_F64)
 // FP64 square root and reciprocal from the hardware estimates refined by
-// Newton-Raphson (Goldschmidt for the root): within an ulp of the correctly
-// rounded results over the arguments the kernels meet (reciprocals of
+// Newton-Raphson (for the root one Goldschmidt iteration, which squares the
+// estimate's error of under 2^-20, and a correction with the exact residual,
+// which squares it again): within an ulp of the correctly rounded results over the
+// arguments the kernels meet (reciprocals of
 // |x| in [1e-13, 1e6], either sign; roots of [1e-20, 1e12]; sqrt(0) = 0),
 // at about half the instructions of the IEEE sequences (-DLESJET_IEEE_F64
 // restores those).
@@ -42,10 +44,7 @@ __device__ __forceinline__ double nr_rcp(double x) {
 __device__ __forceinline__ double nr_sqrt(double x) {
   const double y = __builtin_amdgcn_rsq(x);
   double g = x * y, h = 0.5 * y;
-  double r = fma(-g, h, 0.5);
-  g = fma(g, r, g);
-  h = fma(h, r, h);
-  r = fma(-g, h, 0.5);
+  const double r = fma(-g, h, 0.5);
   g = fma(g, r, g);
   h = fma(h, r, h);
   const double d = fma(-g, g, x);
@@ -180,6 +179,15 @@ __host__ __device__ __forceinline__ T row_dot(int d, const T S[3], T a0, T a1, T
   if (!PROD) return S[0] * a0 + S[1] * a1 + S[2] * a2;
   return d == 0 ? rmul(S[0], a0) : tfma(S[2], a2, rmul(S[1], a1));
 }
+// x -= S . a, x large against the product: the dot product is rounded by
+// itself, so that x is rounded once (a chain of multiply-adds into x rounds it
+// for every term: 19 % more error of a jet residual); FMA: a single term goes
+// into x by one multiply-add.
+template <bool PROD, bool FMA, typename T>
+__host__ __device__ __forceinline__ void row_sub(int d, const T S[3], T a0, T a1, T a2, T& x) {
+  if (FMA && PROD && d == 0) x = tfma(-S[0], a0, x);
+  else x -= row_dot<PROD>(d, S, a0, a1, a2);
+}
 template <bool PROD, typename T>
 __host__ __device__ __forceinline__ T row_norm(int d, const T S[3]) {
   if (!PROD) return tsqrt(S[0] * S[0] + S[1] * S[1] + S[2] * S[2]);
@@ -199,15 +207,17 @@ struct PointIn {
   T S[3][3];         // S[d] = J^-1 grad(xi_d)
   T V;               // J^-1
   T mt, kap;         // held mu + mu_sgs and conductivity (LAG_READ)
+  T iV, len[3], d2;  // product mesh in the FP64 stage kernel: 1 / J^-1, |S[d]|, |J^-1|^(2/3)
 };
 
 // Central differences and pressure sensor along one direction from the
 // (u, v, w, T, p) of the -1 and +1 neighbours; p is the point's pressure.
-template <typename T>
+// STAGE: the differences without the half.
+template <bool STAGE = false, typename T>
 __host__ __device__ __forceinline__ void neighbour_terms(const T m[5], const T pl[5], T p, T dl[4],
                                                          T& nu) {
 #pragma unroll
-  for (int f = 0; f < 4; ++f) dl[f] = T(0.5) * (pl[f] - m[f]);
+  for (int f = 0; f < 4; ++f) dl[f] = STAGE ? pl[f] - m[f] : T(0.5) * (pl[f] - m[f]);
   const T num = pl[4] - T(2) * p + m[4];
   const T den = pl[4] + T(2) * p + m[4];
   nu = tabs(num) * trcp(den);
@@ -244,25 +254,45 @@ struct PointOut {
   T lb[3];
   T nu[3];
   T mt, kap;         // mu + mu_sgs and conductivity of the point (LAG_WRITE)
+  T hiV;             // 1 / (2 J^-1) (STAGE)
 };
 
 // Viscosity update schedule: computed from the point's own state (LAG_NONE),
 // also returned for holding (LAG_WRITE), or taken from held values (LAG_READ).
 enum { LAG_NONE = 0, LAG_WRITE = 1, LAG_READ = 2 };
 
+// x Delta^2, Delta = |J^-1|^(1/3) the filter width.
+template <bool TAB, typename T>
+__host__ __device__ __forceinline__ T filter_sq(T x, const PointIn<T>& in) {
+  if (TAB) return x * in.d2;
+  const T delta = tcbrt(tabs(in.V));
+  return x * delta * delta;
+}
+
 // DYN: the dynamic SGS model's terms are compiled in (used when ph.sgs == 3);
 // a separate instance so that the other models carry none of them.
 // PROD: product mesh (the zero metric terms are not touched); separate for
-// the same reason.  ENTH: in.q[4] holds E + p instead of E.
-template <typename T, int LAG = LAG_NONE, bool DYN = false, bool PROD = false, bool ENTH = false>
+// the same reason.  STAGE: the stage kernel's inputs, in.q[4] = E + p instead of
+// E and in.dl the differences phi_{+1} - phi_{-1} (the halves go into 1 / J^-1);
+// its FP64 form also subtracts single viscous terms by a multiply-add.  With the
+// halves of the differences, of the face averages and of the residual moved
+// into one factor, the root's shorter iteration and no default values for
+// threads without a face, the stage kernel's vector operations per point and
+// plane fell from 942 to 856 (the FP64 kernel is held back by power as well as
+// latency: its clock fell from 2.2 to 1.8 GHz as its stalls went): a step on 102 M
+// points 24.7 -> 23.8 ms, the residual of a 95^3 mesh 59.8 -> 56.7 us.
+template <typename T, int LAG = LAG_NONE, bool DYN = false, bool PROD = false, bool STAGE = false>
 __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phys<T>& ph,
                                                  PointOut<T>& out) {
   Prim<T> s;
   s.rho = in.q[0]; s.u = in.pr[0]; s.v = in.pr[1]; s.w = in.pr[2]; s.p = in.pr[4];
   const T Tt = in.pr[3];
   const T a = tsqrt(Tt);                       // a^2 = gamma p / rho = T
-  const T iV = trcp(in.V);
+  constexpr bool TAB = PROD && STAGE && sizeof(T) == 8;   // tabulated values in `in`
+  const T iV = TAB ? in.iV : trcp(in.V);
   const T aiV = tabs(iV);
+  const T giV = STAGE ? T(0.5) * iV : iV;
+  if (STAGE) out.hiV = giV;
 
   T Uc[3];
 #pragma unroll
@@ -277,7 +307,7 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
       if (PROD && (d == 0) != (m == 0)) out.G[d][1 + m] = rmul(in.q[1 + m], Uc[d]);
       else out.G[d][1 + m] = in.q[1 + m] * Uc[d] + s.p * in.S[d][m];
     }
-    out.G[d][4] = (ENTH ? in.q[4] : in.q[4] + s.p) * Uc[d];
+    out.G[d][4] = (STAGE ? in.q[4] : in.q[4] + s.p) * Uc[d];
   }
 
   if (ph.viscous) {
@@ -289,11 +319,11 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
 #pragma unroll
       for (int m = 0; m < 3; ++m) {
         if (!PROD)
-          g[f][m] = (in.S[0][m] * dl[0][f] + in.S[1][m] * dl[1][f] + in.S[2][m] * dl[2][f]) * iV;
+          g[f][m] = (in.S[0][m] * dl[0][f] + in.S[1][m] * dl[1][f] + in.S[2][m] * dl[2][f]) * giV;
         else if (m == 0)
-          g[f][m] = rmul(in.S[0][0], dl[0][f]) * iV;
+          g[f][m] = rmul(in.S[0][0], dl[0][f]) * giV;
         else
-          g[f][m] = tfma(in.S[2][m], dl[2][f], rmul(in.S[1][m], dl[1][f])) * iV;
+          g[f][m] = tfma(in.S[2][m], dl[2][f], rmul(in.S[1][m], dl[1][f])) * giV;
       }
 
     T mt, kap;
@@ -305,15 +335,12 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
       T mut = T(0);
       if (ph.sgs == 1) {                                      // Smagorinsky
         const T s2 = strain_sq(g);
-        const T delta = tcbrt(tabs(in.V));
-        mut = s.rho * ph.sgs_coef * delta * delta * tsqrt(T(2) * s2);
+        mut = filter_sq<TAB>(s.rho * ph.sgs_coef, in) * tsqrt(T(2) * s2);
       } else if (ph.sgs == 2) {                               // Vreman
-        const T delta = tcbrt(tabs(in.V));
-        mut = s.rho * ph.sgs_coef * delta * delta * vreman_ratio(g);
+        mut = filter_sq<TAB>(s.rho * ph.sgs_coef, in) * vreman_ratio(g);
       } else if (DYN && ph.sgs == 3) {                        // dynamic: C_ds Delta^2 |S|
         const T s2 = strain_sq(g);
-        const T delta = tcbrt(tabs(in.V));
-        mut = s.rho * ph.sgs_coef * delta * delta * tsqrt(T(2) * s2);
+        mut = filter_sq<TAB>(s.rho * ph.sgs_coef, in) * tsqrt(T(2) * s2);
       }
       mt = mu + mut;
       kap = (mu * ph.Pr_inv + mut * ph.Prs_inv) * ph.igm1;
@@ -327,8 +354,7 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
       // (2/3) C_I rho Delta^2 |S|^2 acts as a pressure in the momentum and
       // energy point fluxes (stage |S|, coefficient of the launch)
       const T s2 = strain_sq(g);
-      const T delta = tcbrt(tabs(in.V));
-      const T psgs = ph.iso_coef * s.rho * delta * delta * (T(2) * s2);
+      const T psgs = filter_sq<TAB>(ph.iso_coef * s.rho, in) * (T(2) * s2);
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
 #pragma unroll
@@ -353,17 +379,18 @@ __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phy
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
       const T* Sd = in.S[d];
+      constexpr bool FMA = STAGE && sizeof(T) == 8;
 #pragma unroll
       for (int m = 0; m < 3; ++m)
-        out.G[d][1 + m] -= row_dot<PROD>(d, Sd, tau[m][0], tau[m][1], tau[m][2]);
-      out.G[d][4] -= row_dot<PROD>(d, Sd, beta[0], beta[1], beta[2]);
+        row_sub<PROD, FMA>(d, Sd, tau[m][0], tau[m][1], tau[m][2], out.G[d][1 + m]);
+      row_sub<PROD, FMA>(d, Sd, beta[0], beta[1], beta[2], out.G[d][4]);
     }
   }
 
   // spectral radii and their anisotropic scaling
   T lam[3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) lam[d] = (tabs(Uc[d]) + a * row_norm<PROD>(d, in.S[d])) * aiV;
+  for (int d = 0; d < 3; ++d) lam[d] = (tabs(Uc[d]) + a * (TAB ? in.len[d] : row_norm<PROD>(d, in.S[d]))) * aiV;
   // lambda_d + sqrt(lambda_d lambda_e) + sqrt(lambda_d lambda_f)
   //   = sqrt(lambda_d) (sqrt(lambda_d) + sqrt(lambda_e) + sqrt(lambda_f))
   const T r0 = tsqrt(lam[0]), r1 = tsqrt(lam[1]), r2 = tsqrt(lam[2]);
@@ -382,23 +409,34 @@ __host__ __device__ __forceinline__ void wvec(const T q[5], const Phys<T>& ph, T
   W[0] = q[0]; W[1] = q[1]; W[2] = q[2]; W[3] = q[3]; W[4] = q[4] + s.p;
 }
 
-// Numerical flux at the face between L and R = L + 1 along one direction.
+// Twice the numerical flux at the face between L and R = L + 1 along one
+// direction (the halves of the averages left to the caller: exact scaling).
 template <typename T>
-__host__ __device__ __forceinline__ void face_flux(const T GL[5], const T GR[5], T lbL, T lbR,
+__host__ __device__ __forceinline__ void face_flux2(const T GL[5], const T GR[5], T lbL, T lbR,
                                                    T nuL, T nuR, T VL, T VR, const T Wm[5],
                                                    const T WL[5], const T WR[5], const T Wp[5],
                                                    bool physical, const Phys<T>& ph, T F[5]) {
   const T e2 = ph.k2 * tmax(nuL, nuR);
   const T e4 = tmax(T(0), ph.k4 - e2);
-  const T lf = T(0.5) * (lbL + lbR);
+  const T lf2 = lbL + lbR;
   const T Vf = physical ? T(0) : T(0.5) * (VL + VR);
-  // V_f d = a2 (W_R - W_L) - a4 ((W_{R+1} - W_{L-1}) - 3 (W_R - W_L))
-  const T vl = Vf * lf, a2 = vl * e2, a4 = vl * e4;
+  // V_f d = a2 (W_R - W_L) - a4 ((W_{R+1} - W_{L-1}) - 3 (W_R - W_L)), doubled
+  const T vl = Vf * lf2, a2 = vl * e2, a4 = vl * e4;
+#pragma unroll
   for (int c = 0; c < 5; ++c) {
     const T A = WR[c] - WL[c];
     const T B = (Wp[c] - Wm[c]) - T(3) * A;
-    F[c] = T(0.5) * (GL[c] + GR[c]) - a2 * A + a4 * B;
+    F[c] = (GL[c] + GR[c]) - a2 * A + a4 * B;
   }
+}
+
+template <typename T>
+__host__ __device__ __forceinline__ void face_flux(const T GL[5], const T GR[5], T lbL, T lbR,
+                                                   T nuL, T nuR, T VL, T VR, const T Wm[5],
+                                                   const T WL[5], const T WR[5], const T Wp[5],
+                                                   bool physical, const Phys<T>& ph, T F[5]) {
+  face_flux2(GL, GR, lbL, lbR, nuL, nuR, VL, VR, Wm, WL, WR, Wp, physical, ph, F);
+  for (int c = 0; c < 5; ++c) F[c] *= T(0.5);
 }
 
 // Sum of the spectral radii lambda_xi + lambda_eta + lambda_zeta at a point

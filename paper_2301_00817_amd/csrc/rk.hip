@@ -29,7 +29,8 @@ __global__ void k_lambda_max(const TQ* __restrict__ Q, const TM* __restrict__ M,
     double V;
     if (PROD) {     // the stored terms are those of the storage type
       double m[10];
-      product_terms(pt.x[i + NG], pt.yz + (long long)(k + NG) * prod_plane(g) + (j + NG) * 4, m);
+      product_terms(pt.x[(i + NG) * PX_N], pt.yz + (long long)(k + NG) * prod_plane(g) + (j + NG) * PT_N,
+                    m);
       for (int d = 0; d < 3; ++d)
         for (int c = 0; c < 3; ++c) S[d][c] = (double)(TM)m[3 * d + c];
       V = (double)(TM)m[9];
