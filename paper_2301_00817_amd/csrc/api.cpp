@@ -657,19 +657,14 @@ static int rk5_steps(les_ctx* c, double* Qn, int nsteps, double dt_fixed, double
   T* B[3] = {(T*)c->stage[0], (T*)c->stage[1], (T*)c->stage[2]};
   const T* M = (const T*)c->M;
   hipError_t e = launch_reset(c->maxbits, c->flag, s);
-  // FP32 storage: the stage-0 state is an FP32 copy of Q^n
-  T* cur = (T*)Qn;
-  if (fp32 && e == hipSuccess) {
-    e = launch_to_float(Qn, (float*)B[1], (long long)5 * c->g.vs, s);
-    cur = B[1];
-  }
+  // first pass over Q^n: the reduction of the first step's dt (later steps
+  // take the maximum accumulated by the previous step's last stage); FP32
+  // storage: the stage-0 state is an FP32 copy of Q^n
+  T* cur = fp32 ? B[1] : (T*)Qn;
+  if (e == hipSuccess && (cfl || fp32))
+    e = launch_first_pass<T>(Qn, M, c->g, c->ph64, cfl, c->maxbits, fp32 ? (float*)B[1] : nullptr,
+                             c->pt, s);
   for (int n = 0; n < nsteps && e == hipSuccess; ++n) {
-    // dt of this step: the first step reduces over Q^n here, later steps
-    // take the maximum accumulated by the previous step's last stage
-    if (cfl && n == 0) {
-      if (fp32) e = launch_lambda_max<double, float>(Qn, (const float*)c->M, c->g, c->ph64, c->maxbits, c->pt, s);
-      else e = launch_lambda_max<double, double>(Qn, (const double*)c->M, c->g, c->ph64, c->maxbits, c->pt, s);
-    }
     if (e == hipSuccess)
       e = launch_dt_finalize(c->maxbits, c->p.cfl, dt_fixed, c->dt, dt_out ? dt_out + n : nullptr,
                              c->flag, s);
@@ -745,10 +740,10 @@ int les_diagnostics(les_ctx* c, const double* Qn, double* totals, double* sum1, 
   hipError_t e;
   if (c->p.precision == LES_FP32_STORAGE)
     e = launch_diagnostics<float>(Qn, (const float*)c->M, c->g, c->ph64, c->part, totals, sum1,
-                                  sum2, (hipStream_t)stream);
+                                  sum2, c->pt, (hipStream_t)stream);
   else
     e = launch_diagnostics<double>(Qn, (const double*)c->M, c->g, c->ph64, c->part, totals, sum1,
-                                   sum2, (hipStream_t)stream);
+                                   sum2, c->pt, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(c, e, "diagnostics kernels");
   return LES_OK;
 }
@@ -769,10 +764,10 @@ int les_diagnostics_noalloc(les_ctx* c, const double* Qn, double* totals, double
   hipError_t e;
   if (c->p.precision == LES_FP32_STORAGE)
     e = launch_diagnostics<float>(Qn, (const float*)c->M, c->g, c->ph64, c->part_static, totals,
-                                  sum1, sum2, (hipStream_t)stream);
+                                  sum1, sum2, c->pt, (hipStream_t)stream);
   else
     e = launch_diagnostics<double>(Qn, (const double*)c->M, c->g, c->ph64, c->part_static, totals,
-                                   sum1, sum2, (hipStream_t)stream);
+                                   sum1, sum2, c->pt, (hipStream_t)stream);
   if (e != hipSuccess) return hip_fail(c, e, "diagnostics kernels");
   return LES_OK;
 }

@@ -71,9 +71,12 @@ enum { FUSED_EPI_R = 0, FUSED_EPI_RK = 1, FUSED_EPI_RK_LAST = 2 };
 // point formulas): none, write the held values, read them
 enum { FUSED_LAG_NONE = 0, FUSED_LAG_WRITE = 1, FUSED_LAG_READ = 2 };
 
-template <typename TQ, typename TM>
-hipError_t launch_lambda_max(const TQ* Q, const TM* M, const Grid& g, const Phys<double>& ph,
-                             unsigned long long* maxbits, const ProdTab& pt, hipStream_t s);
+// Reduction for the first dt of a call (lambda) and, if Q32 is given, the
+// FP32 copy of the interior of Q.
+template <typename TM>
+hipError_t launch_first_pass(const double* Q, const TM* M, const Grid& g, const Phys<double>& ph,
+                             bool lambda, unsigned long long* maxbits, float* Q32,
+                             const ProdTab& pt, hipStream_t s);
 
 hipError_t launch_dt_finalize(unsigned long long* maxbits, double cfl, double dt_fixed,
                               double* dt, double* dt_out, int* flag, hipStream_t s);
@@ -91,7 +94,8 @@ int diag_partials(const Grid& g);
 
 template <typename TM>
 hipError_t launch_diagnostics(const double* Q, const TM* M, const Grid& g, const Phys<double>& ph,
-                              double* part, double* totals, double* s1, double* s2, hipStream_t s);
+                              double* part, double* totals, double* s1, double* s2,
+                              const ProdTab& pt, hipStream_t s);
 
 // Residual adjoint (FP64): Qb = (dR/dQ)^T Rb on the padded layout (ghost
 // entries zero); inflow_bar (5, nth, nr) accumulated when non-null.  Scratch
@@ -108,7 +112,5 @@ hipError_t launch_residual_vjp(const double* Q, const double* M, const Grid& g,
 hipError_t launch_scale(const double* x, double a, double* y, long long n, hipStream_t s);
 hipError_t launch_interior_copy(const double* x, double* y, const Grid& g, hipStream_t s);
 hipError_t launch_accumulate(const double* x, double* y, long long n, hipStream_t s);
-
-hipError_t launch_to_float(const double* a, float* b, long long n, hipStream_t s);
 
 }  // namespace lesjet
