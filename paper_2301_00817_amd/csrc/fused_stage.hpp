@@ -27,7 +27,7 @@
 
 #include "launch.hpp"
 #include "physics.hpp"
-#include "plane_io.hpp"
+#include "tiles.hpp"
 
 namespace lesjet {
 
@@ -46,15 +46,6 @@ enum { EPI_R = 0, EPI_RK = 1, EPI_RK_LAST = 2 };
 // Global memory is addressed plane by plane (plane_io.hpp): one 32-bit
 // offset register per column serves every variable and plane of the march.
 
-// Byte offset of a column a thread reads: outside the padded box the nearest
-// point of it (finite data that no output uses; clamping instead of a
-// default value spares the moves that would set the default before every
-// load).
-template <typename T>
-__device__ __forceinline__ unsigned q_col(const Grid& g, int i, int j) {
-  return col_off<T>(g, min(max(i, -NG), g.nx + NG - 1), min(max(j, -NG), g.nr + NG - 1));
-}
-
 template <typename T>
 __device__ __forceinline__ void load_q(const T* Q, const Grid& g, unsigned col, int k, T q[5]) {
 #pragma unroll
@@ -68,34 +59,6 @@ __device__ __forceinline__ void load_metrics(const T* M, const Grid& g, unsigned
   for (int c = 0; c < 10; ++c) m[c] = gld(M, g, c, k, col);
 }
 
-// Value of the lane one column to the left (right) in a tile row of X threads:
-// a data-parallel move within the wave (16-lane rows, or the whole wave where
-// a row is 32 lanes), executed with every lane active.  The first (last) lane
-// of a row gets zero or another row's value, which nothing uses.
-template <int CTRL>
-__device__ __forceinline__ int lane_mov(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xf, 0xf, true);
-}
-template <int CTRL>
-__device__ __forceinline__ float lane_mov(float v) {
-  return __builtin_bit_cast(float, lane_mov<CTRL>(__builtin_bit_cast(int, v)));
-}
-template <int CTRL>
-__device__ __forceinline__ double lane_mov(double v) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = lane_mov<CTRL>((int)b), hi = lane_mov<CTRL>((int)(b >> 32));
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned)lo);
-}
-template <int X, typename T>
-__device__ __forceinline__ T from_left(T v) {
-  static_assert(X == 16 || X == 32, "tile rows of 16 or 32 lanes");
-  return lane_mov<X == 16 ? 0x111 : 0x138>(v);      // row_shr:1, wave_shr:1
-}
-template <int X, typename T>
-__device__ __forceinline__ T from_right(T v) {
-  return lane_mov<X == 16 ? 0x101 : 0x130>(v);      // row_shl:1, wave_shl:1
-}
-
 // s_waitcnt operand: no vector memory access outstanding (LDS and scalar
 // counters not waited for).  The compiler places its waits for the fewest
 // accesses issued on any path; the loads of the march sit in branches, so a
@@ -106,17 +69,6 @@ __device__ __forceinline__ T from_right(T v) {
 // behind a store.  8 % of the FP64 step with held viscosities on 1.0 M points,
 // 3-4 % of the steps on 102 M (FP64) and 23.6 M points (FP32).
 constexpr int WAIT_VMEM = 0x0F70;
-
-// Workgroups are dealt to the eight XCDs (each with its own L2) in turn.  The
-// hardware id is remapped so that XCD x receives a contiguous run of tiles,
-// i fastest, then j, then the k-chunk: tiles that share halos run at the
-// same time on the same L2.
-constexpr int NXCD = 8;
-
-struct TileMap {
-  int gx, gy, gz;       // tiles along i, j and k-chunks
-  int per_xcd;          // ceil(gx gy gz / NXCD)
-};
 
 // The FP64 kernel has registers left at two waves per SIMD: it loads Q^(0)
 // of the output point an iteration ahead (FP32 at 128 VGPRs does not, nor
@@ -211,12 +163,8 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
 
   const int tx = threadIdx.x, ty = threadIdx.y;
   const int tid = ty * FB_X + tx;
-  const int hw = blockIdx.x;
-  const int tile = (hw % NXCD) * tm.per_xcd + hw / NXCD;
-  if (tile >= tm.gx * tm.gy * tm.gz) return;          // uniform for the block
-  const int bx = tile % tm.gx;
-  const int by = (tile / tm.gx) % tm.gy;
-  const int bz = tile / (tm.gx * tm.gy);
+  int bx, by, bz;
+  if (!tile_of_block(tm, bx, by, bz)) return;         // uniform for the block
   const int i0 = bx * FT_X, j0 = by * FT_Y;
   const int k0 = bz * kc;
   const int k1 = min(k0 + kc, g.nth);
@@ -594,10 +542,14 @@ int fused_chunk(const Grid& g, int num_cu) {
                                       // three per CU, takes the same length)
   const long long tiles = (long long)((g.nx + FT_X - 1) / FT_X) * ((g.nr + FT_Y - 1) / FT_Y);
   // pick the chunk length that minimises (rounds of resident blocks) x (planes per block),
-  // over every length from 4 planes to the cap (lengths that divide the
-  // azimuth leave no short last chunk: against powers of two only, 5.6 % on
-  // the 128 x 128 x 360 mesh and 3.1 % on 1700 x 1700 x 360 in FP64, 1.4-1.6 %
-  // in FP32, 0.5 % on 1250 x 640 x 1250).
+  // over every length up to the cap (a mesh that fits one round takes the
+  // shortest chunks that still do: 32^3, single planes, three iterations per
+  // block, 15.8 us a residual against 20.1 us with four; FP32 keeps at least
+  // four, as its states depend on the chunk length by up to 6e-8, the rounding of
+  // a chunk's first planes in its prologue; lengths that divide the azimuth
+  // leave no short last chunk: against powers of two only, 5.6 % on the 128 x
+  // 128 x 360 mesh and 3.1 % on 1700 x 1700 x 360 in FP64, 1.4-1.6 % in FP32,
+  // 0.5 % on 1250 x 640 x 1250).
   // FP32 (four blocks per CU) stops at 16 planes: longer chunks measured
   // slower on large meshes (4 % at 1e8 points, 8 % at 1e9), the resident
   // blocks of a round drifting apart in k and sharing fewer halo lines in
@@ -609,7 +561,7 @@ int fused_chunk(const Grid& g, int num_cu) {
     int best = g.nth;
     long long best_rounds = 0;
     double best_cost = 1e300;
-    for (int kc = 4; kc <= kc_max; ++kc) {
+    for (int kc = sizeof(T) == 8 ? 1 : 4; kc <= kc_max; ++kc) {
       const long long nb = tiles * ((g.nth + kc - 1) / kc);
       const long long rounds = (nb + num_cu - 1) / num_cu;
       const double cost = (double)rounds * (kc + 2);
@@ -635,12 +587,8 @@ hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph
   if (lag != LAG_NONE && (!visc || epi == EPI_R || (lag == LAG_WRITE && epi != EPI_RK)))
     return hipErrorInvalidValue;
   constexpr int FT_X = Tile<T>::X - 2, FT_Y = Tile<T>::Y - 2;
-  TileMap tm;
-  tm.gx = (g.nx + FT_X - 1) / FT_X;
-  tm.gy = (g.nr + FT_Y - 1) / FT_Y;
-  tm.gz = (g.nth + kc - 1) / kc;
-  const long long ntiles = (long long)tm.gx * tm.gy * tm.gz;
-  tm.per_xcd = (int)((ntiles + NXCD - 1) / NXCD);
+  const TileMap tm = tile_map((g.nx + FT_X - 1) / FT_X, (g.nr + FT_Y - 1) / FT_Y,
+                              (g.nth + kc - 1) / kc);
   const dim3 grid((unsigned)(tm.per_xcd * NXCD));
   const dim3 block(Tile<T>::X, Tile<T>::Y, 1);
 #define LESJET_FUSED_P(E, A, L, D, P)                                                  \

@@ -191,7 +191,9 @@ __host__ __device__ __forceinline__ void row_sub(int d, const T S[3], T a0, T a1
 template <bool PROD, typename T>
 __host__ __device__ __forceinline__ T row_norm(int d, const T S[3]) {
   if (!PROD) return tsqrt(S[0] * S[0] + S[1] * S[1] + S[2] * S[2]);
-  return d == 0 ? tabs(S[0]) : tsqrt(tfma(S[2], S[2], rmul(S[1], S[1])));
+  // (FP32: the hardware root of the square, an ulp off |S[0]|, as the general form)
+  if (d == 0) return sizeof(T) == 4 ? tsqrt(rmul(S[0], S[0])) : tabs(S[0]);
+  return tsqrt(tfma(S[2], S[2], rmul(S[1], S[1])));
 }
 
 // Data a point needs: its state and primitives, the central differences of
@@ -426,7 +428,10 @@ __host__ __device__ __forceinline__ void face_flux2(const T GL[5], const T GR[5]
   for (int c = 0; c < 5; ++c) {
     const T A = WR[c] - WL[c];
     const T B = (Wp[c] - Wm[c]) - T(3) * A;
-    F[c] = (GL[c] + GR[c]) - a2 * A + a4 * B;
+    // FP32 (rounded as the undoubled form contracted: the rounding of a stage
+    // state turns any difference into one of an ulp)
+    if (sizeof(T) == 4) F[c] = radd(GL[c] + GR[c], -rmul(a2, A)) + a4 * B;
+    else F[c] = (GL[c] + GR[c]) - a2 * A + a4 * B;
   }
 }
 
