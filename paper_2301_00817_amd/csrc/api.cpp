@@ -519,7 +519,7 @@ static int dynamic_ready(les_ctx* c) {
   int r = dalloc(c, (void**)&c->dyn_scr, (size_t)DYN_SCRATCH_VARS * c->g.vs * sizeof(double),
                  "dynamic-model scratch");
   if (r == LES_OK)
-    r = dalloc(c, (void**)&c->dyn_part, (size_t)7 * dyn_blocks(c->g) * sizeof(double),
+    r = dalloc(c, (void**)&c->dyn_part, (size_t)7 * dyn_blocks(c->g, c->num_cu) * sizeof(double),
                "dynamic-model sums");
   if (r == LES_OK) r = dalloc(c, (void**)&c->dyn, DYN_COEF_DOUBLES * sizeof(double), "dynamic coefficients");
   return r;
@@ -529,7 +529,7 @@ static int dynamic_ready(les_ctx* c) {
 template <typename T>
 static hipError_t dynamic_coefs(les_ctx* c, const T* Q, hipStream_t s) {
   return launch_dynamic<T>(Q, (const T*)c->M, c->g, c->p.gamma, c->p.visc_coef, c->p.Pr_sgs,
-                           c->dyn_scr, c->dyn_part, c->dyn, s);
+                           c->dyn_scr, c->dyn_part, c->dyn, c->num_cu, c->pt, s);
 }
 
 // R(Q) into R_out (ghosts of Q filled first), fused kernel.

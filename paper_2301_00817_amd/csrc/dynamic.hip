@@ -8,336 +8,428 @@
 // fixed-order trees (reproducible).
 //
 // The separable filter is applied one direction at a time:
-//   k_dyn_plane   per 32 x 8 tile of a plane, the primitives of the tile
-//                 and two rings staged once in LDS: rho |S| S_ij,
-//                 rho |S|^2, rho |S| dT/dx_j (central differences and the
-//                 chain rule) formed once per point of the tile and its ring
-//                 into LDS; rho, rho u_i, rho T, rho u_i u_j, rho u_i T
-//                 formed from the staged primitives where read; all filtered
-//                 along i and j and stored;
-//   k_dyn_hat     points of [-1, n]^3: the filter along k of rho, rho u_i,
-//                 rho T -> hat(rho), hat(rho u_i), hat(rho T);
-//   k_dyn_sums    interior points: the filter along k of the other fields,
-//                 the strain of u_hat = hat(rho u)/hat(rho) and the gradient
-//                 of T_hat = hat(rho T)/hat(rho); per block, the
-//                 J^-1-weighted sums of the seven numerator and denominator
-//                 terms;
-//   k_dyn_final   one block: the sums, the coefficients, clipping.
+//   k_dyn_hat     points of [-1, n]^3: the state fields rho, rho u_i, rho T
+//                 filtered along j (LDS), i (lane moves) and k (registers,
+//                 marching over planes) -> hat(rho), hat(rho u_i), hat(rho T);
+//   k_dyn_terms   the stage kernel's march: per plane each ring-1 column forms
+//                 rho |S| S_ij, rho |S|^2, rho |S| dT/dx_j, rho u_i u_j and
+//                 rho u_i T, filters them along i (lane moves), j (LDS) and k
+//                 (registers); with the strain of u_hat = hat(rho u)/hat(rho) and
+//                 the gradient of T_hat = hat(rho T)/hat(rho) the J^-1-weighted
+//                 numerator and denominator terms of the plane before are
+//                 added up in registers, one set of seven sums per block (two
+//                 launches, one per group of fields);
+//   k_dyn_final   the sums, the coefficients, clipping.
+// Only the five filtered state fields pass through memory.  (Filtering along
+// i and j in one pass, 24 fields stored, and along k in two more took 0.48 ms
+// on 2.05 M points, bound by those fields' 440 MB written and re-read at
+// three planes; these passes take 0.044 + 0.098 + 0.068 ms.)
 #include "launch.hpp"
 #include "physics.hpp"
+#include "tiles.hpp"
 
 namespace lesjet {
 
-// Fields filtered along i and j (index within the 24 filtered fields and
-// scratch variable), then the fully filtered state.
-enum {
-  DY_FS = 0,     // rho |S| S_ij, ij = 00 11 22 01 02 12    (i, j in [0, n), k in [-1, n])
-  DY_FS2 = 6,    // rho |S|^2
-  DY_FT = 7,     // rho |S| dT/dx_j
-  DY_PUU = 10,   // rho u_i u_j, ij = 00 11 22 01 02 12
-  DY_PUT = 16,   // rho u_i T
-  DY_NG = 19,    // fields used at interior points only
-  DY_R = 19,     // rho, rho u_i, rho T                      (i, j in [-1, n], every plane)
-  DY_NF = 24,
-  DY_HR = 24,    // hat(rho)                                 ([-1, n]^3)
-  DY_HRU = 25,   // hat(rho u_i)
-  DY_HRT = 28,   // hat(rho T)
-  DY_N = 29
-};
+// Scratch variables: the filtered state on [-1, n]^3.
+enum { DY_HR = 0, DY_HRU = 1, DY_HRT = 4, DY_N = 5 };
 static_assert(DY_N == DYN_SCRATCH_VARS, "dynamic-model scratch size");
 
+// Fields of a plane: rho |S| S_ij, rho |S|^2, rho |S| dT/dx_j, rho u_i u_j,
+// rho u_i T (ij = 00 11 22 01 02 12)
+enum { DF_S = 0, DF_S2 = 6, DF_T = 7, DF_UU = 10, DF_UT = 16, DF_N = 19 };
+
 constexpr int DY_BS = 256;
-constexpr int DY_NXCD = 8;   // XCDs of the device (workgroups are dealt to them in turn)
 constexpr int DY_NSUM = 7;   // N_I, D_I, A, B, D_d, N_P, D_P
 static_assert(DY_NSUM + 6 + 3 <= DYN_COEF_DOUBLES, "coefficient buffer size");
 
-constexpr double FW[3] = {0.25, 0.5, 0.25};   // test-filter weights
-
-struct PrimD {
-  double rho, u, v, w, T, p;
-};
-
-template <typename T>
-__device__ __forceinline__ PrimD prim_at(const T* __restrict__ Q, const Grid& g, int o,
-                                         double gamma) {
-  PrimD s;
-  const double q0 = (double)Q[o], q1 = (double)Q[(long long)g.vs + o],
-               q2 = (double)Q[2LL * g.vs + o], q3 = (double)Q[3LL * g.vs + o],
-               q4 = (double)Q[4LL * g.vs + o];
-  const double ir = trcp(q0);          // one reciprocal per point
-  s.rho = q0;
-  s.u = q1 * ir;
-  s.v = q2 * ir;
-  s.w = q3 * ir;
-  s.p = (gamma - 1.0) * (q4 - 0.5 * q0 * (s.u * s.u + s.v * s.v + s.w * s.w));
-  s.T = gamma * s.p * ir;
-  return s;
+// Test filter (1/4, 1/2, 1/4) of three neighbouring values.
+__device__ __forceinline__ double filt(double l, double c, double r) {
+  return fma(0.25, l + r, 0.5 * c);
 }
 
-// Velocity and temperature gradients at o from the central differences
-// dl[d] of (u, v, w, T) along the three index directions (chain rule with
-// the metrics of o).
 template <typename T>
-__device__ __forceinline__ void chain_rule(const double dl[3][4], const T* __restrict__ M,
-                                           const Grid& g, int o, double gu[3][3], double gT[3]) {
-  const double iV = trcp((double)M[9LL * g.vs + o]);
-  for (int m = 0; m < 3; ++m) {
-    const double S0 = (double)M[(long long)m * g.vs + o];
-    const double S1 = (double)M[(long long)(3 + m) * g.vs + o];
-    const double S2 = (double)M[(long long)(6 + m) * g.vs + o];
-    for (int f = 0; f < 3; ++f) gu[f][m] = (S0 * dl[0][f] + S1 * dl[1][f] + S2 * dl[2][f]) * iV;
-    gT[m] = (S0 * dl[0][3] + S1 * dl[1][3] + S2 * dl[2][3]) * iV;
+__device__ __forceinline__ void load5(const T* __restrict__ Q, const Grid& g, unsigned col, int k,
+                                      double q[5]) {
+#pragma unroll
+  for (int c = 0; c < 5; ++c) q[c] = (double)gld(Q, g, c, k, col);
+}
+
+// rho, u, v, w, T of a state.
+__device__ __forceinline__ void prim_t(const double q[5], double gamma, double p[5]) {
+  const double ir = trcp(q[0]);
+  p[0] = q[0];
+  p[1] = q[1] * ir;
+  p[2] = q[2] * ir;
+  p[3] = q[3] * ir;
+  p[4] = gamma * ((gamma - 1.0) * (q[4] - 0.5 * q[0] * (p[1] * p[1] + p[2] * p[2] + p[3] * p[3]))) * ir;
+}
+
+// The chunks of planes: (rounds of resident blocks) x (planes per block).
+static int dyn_chunk(long long tiles, int nth, int resident, int extra) {
+  int best = nth;
+  double best_cost = 1e300;
+  for (int kc = 1; kc <= 64 && kc <= nth; ++kc) {
+    const long long nb = tiles * ((nth + kc - 1) / kc);
+    const double cost = (double)((nb + resident - 1) / resident) * (kc + extra);
+    if (cost < best_cost) { best_cost = cost; best = kc; }
   }
+  return best;
 }
 
-// Resolved gradients at o, the neighbours' primitives from global memory.
+// Filtered state.  A block's rows of 32 threads hold the columns of 30
+// outputs and one neighbour on each side; the rows above and below the tile
+// are loaded by its first wave.
+constexpr int DH_X = 32, DH_Y = 8;
 template <typename T>
-__device__ __forceinline__ void gradients(const T* __restrict__ Q, const T* __restrict__ M,
-                                          const Grid& g, int o, double gamma, double gu[3][3],
-                                          double gT[3]) {
-  const int step[3] = {1, g.pitch, g.plane};
-  double dl[3][4];
-  for (int d = 0; d < 3; ++d) {
-    const PrimD a = prim_at(Q, g, o + step[d], gamma), b = prim_at(Q, g, o - step[d], gamma);
-    dl[d][0] = 0.5 * (a.u - b.u);
-    dl[d][1] = 0.5 * (a.v - b.v);
-    dl[d][2] = 0.5 * (a.w - b.w);
-    dl[d][3] = 0.5 * (a.T - b.T);
-  }
-  chain_rule(dl, M, g, o, gu, gT);
-}
-
-__device__ __forceinline__ void strain(const double gu[3][3], double S[3][3], double& Smag) {
-  double s2 = 0.0;
-  for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) {
-      S[i][j] = 0.5 * (gu[i][j] + gu[j][i]);
-      s2 += S[i][j] * S[i][j];
+__global__ __launch_bounds__(DH_X * DH_Y) void k_dyn_hat(const T* __restrict__ Q, Grid g,
+                                                         double gamma, int kc, TileMap tm,
+                                                         double* __restrict__ SC) {
+  __shared__ double sF[2][5][DH_Y + 2][DH_X];
+  const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * DH_X + tx;
+  int bx, by, bz;
+  if (!tile_of_block(tm, bx, by, bz)) return;
+  // outputs i0 .. i0 + 29, j0 .. j0 + 7 of [-1, n]
+  const int i0 = bx * (DH_X - 2) - 1, j0 = by * DH_Y - 1;
+  const int k0 = bz * kc - 1, k1 = min(k0 + kc, g.nth + 1);
+  const int i = i0 - 1 + tx, j = j0 + ty;
+  const bool out = tx >= 1 && tx <= DH_X - 2 && i <= g.nx && j <= g.nr;
+  const bool has_b = tid < 2 * DH_X;
+  const int bry = tid < DH_X ? 0 : DH_Y + 1;
+  const unsigned oq = q_col<T>(g, i, j), oob = q_col<T>(g, i0 - 1 + (tid & (DH_X - 1)), j0 - 1 + bry);
+  const unsigned o64 = q_col<double>(g, i, j);
+  // rho, rho u_i and rho T = gamma p of a state
+  auto fields = [&](double q[5]) {
+    q[4] = gamma * ((gamma - 1.0) *
+                    (q[4] - 0.5 * (q[1] * q[1] + q[2] * q[2] + q[3] * q[3]) * trcp(q[0])));
+  };
+  double q[5], b[5], fm[5] = {0, 0, 0, 0, 0}, fc[5] = {0, 0, 0, 0, 0};
+  load5(Q, g, oq, k0 - 1, q);
+  if (has_b) load5(Q, g, oob, k0 - 1, b);
+  for (int kk = k0 - 1, buf = 0; kk <= k1; ++kk, buf ^= 1) {
+    fields(q);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) sF[buf][c][ty + 1][tx] = q[c];
+    if (has_b) {
+      fields(b);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) sF[buf][c][bry][tid & (DH_X - 1)] = b[c];
     }
-  Smag = tsqrt(2.0 * s2);
+    double f[5];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) f[c] = q[c];
+    if (kk < k1) {
+      load5(Q, g, oq, kk + 1, q);
+      if (has_b) load5(Q, g, oob, kk + 1, b);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      f[c] = filt(sF[buf][c][ty][tx], f[c], sF[buf][c][ty + 2][tx]);
+      f[c] = filt(from_left<DH_X>(f[c]), f[c], from_right<DH_X>(f[c]));
+    }
+    if (out && kk > k0) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) gst(SC, g, DY_HR + c, kk - 1, o64, filt(fm[c], fc[c], f[c]));
+    }
+#pragma unroll
+    for (int c = 0; c < 5; ++c) { fm[c] = fc[c]; fc[c] = f[c]; }
+  }
 }
 
-// Tiles of the columns [-2, n] x [-1, n] of a plane; every padded plane.
-// Gradient fields on the tile and a one-point ring (DP_*), primitives on the
-// tile and a two-point ring (DQ_*).
-constexpr int DP_X = 32, DP_Y = 8, DP_HX = DP_X + 2, DP_HY = DP_Y + 2, DP_HP = DP_HX * DP_HY;
-constexpr int DQ_HX = DP_X + 4, DQ_HY = DP_Y + 4, DQ_HP = DQ_HX * DQ_HY;
+// Gradients of (u, v, w, T) from the undivided central differences dl[d], by
+// the chain rule with the metric terms m and hiV = 1 / (2 J^-1).
+template <bool PROD>
+__device__ __forceinline__ void chain_rule(const double dl[3][4], const double m[10], double hiV,
+                                           double g[4][3]) {
+#pragma unroll
+  for (int f = 0; f < 4; ++f)
+#pragma unroll
+    for (int x = 0; x < 3; ++x) {
+      if (!PROD) g[f][x] = (m[x] * dl[0][f] + m[3 + x] * dl[1][f] + m[6 + x] * dl[2][f]) * hiV;
+      else if (x == 0) g[f][x] = m[0] * dl[0][f] * hiV;
+      else g[f][x] = (m[3 + x] * dl[1][f] + m[6 + x] * dl[2][f]) * hiV;
+    }
+}
 
-template <typename T>
-__global__ __launch_bounds__(DP_X * DP_Y) void k_dyn_plane(const T* __restrict__ Q,
-                                                           const T* __restrict__ M, Grid g,
-                                                           double gamma, int tiles_x,
-                                                           double* __restrict__ SC) {
-  __shared__ double sP[5][DQ_HP];          // rho, u, v, w, T
-  __shared__ double sG[DY_PUU][DP_HP];     // rho |S| S_ij, rho |S|^2, rho |S| dT/dx_j
-  // tile columns start at padded index 0 (i = -2) so that each tile row is
-  // whole 128-byte lines of the scratch arrays
-  const int i0 = (blockIdx.x % tiles_x) * DP_X - NG, j0 = (blockIdx.x / tiles_x) * DP_Y - 1;
-  const int k = (int)blockIdx.y - NG;
-  // the gradient fields are needed on the planes [-1, n] (uniform per block)
-  const bool kgrad = k >= -1 && k <= g.nth;
-  const int tid = threadIdx.x;
-  // primitives of the tile and two rings, clamped to the padded box (a
-  // clamped slot feeds no stored value)
-  for (int e = tid; e < DQ_HP; e += DP_X * DP_Y) {
-    const int i = min(i0 - 2 + e % DQ_HX, g.nx + 1), j = min(j0 - 2 + e / DQ_HX, g.nr + 1);
-    const PrimD s = prim_at(Q, g, g.at(max(i, -NG), max(j, -NG), k), gamma);
-    sP[0][e] = s.rho;
-    sP[1][e] = s.u;
-    sP[2][e] = s.v;
-    sP[3][e] = s.w;
-    sP[4][e] = s.T;
+// S_ij (00 11 22 01 02 12) and |S| = sqrt(2 S_ij S_ij).
+__device__ __forceinline__ void strain6(const double g[4][3], double S[6], double& Smag) {
+  S[0] = g[0][0];
+  S[1] = g[1][1];
+  S[2] = g[2][2];
+  S[3] = 0.5 * (g[0][1] + g[1][0]);
+  S[4] = 0.5 * (g[0][2] + g[2][0]);
+  S[5] = 0.5 * (g[1][2] + g[2][1]);
+  Smag = tsqrt(2.0 * (S[0] * S[0] + S[1] * S[1] + S[2] * S[2] +
+                      2.0 * (S[3] * S[3] + S[4] * S[4] + S[5] * S[5])));
+}
+
+// Whether sum q is of this part of k_dyn_terms.
+__device__ __forceinline__ bool part_sum(int part, int q) {
+  return (q == 0 || q == 2 || q == 6) == (part == 1);
+}
+
+constexpr int DT_X = 16, DT_Y = 16, DT_RX = DT_X + 2, DT_RY = DT_Y + 2;
+constexpr int DT_BORDER = DT_RX * DT_RY - DT_X * DT_Y;
+
+// PART 0: the strain fields (DF_S .. DF_T) and the terms of u_hat and T_hat
+// -> D_I, B, D_d, N_P; PART 1: the products (DF_UU, DF_UT) -> N_I, A, D_P.  One
+// pass over all 19 fields needs more than an FP64 wave's 256 registers (78 spilled:
+// 0.35 ms on 2.05 M points against 0.17 ms for the two parts, which form the
+// resolved strain twice; at three waves per SIMD they spill again, 0.65 ms).
+template <typename T, bool PROD, int PART>
+__global__ __launch_bounds__(DT_X * DT_Y, 2) void k_dyn_terms(
+    const T* __restrict__ Q, const T* __restrict__ M, Grid g, double gamma, int kc, TileMap tm,
+    ProdTab pt, const double* __restrict__ SC, double* __restrict__ part) {
+  __shared__ double sP[4][DT_RY][DT_RX];       // u, v, w, T of plane kk
+  constexpr int F0 = PART == 0 ? DF_S : DF_UU, FN = PART == 0 ? DF_UU - DF_S : DF_N - DF_UU;
+  __shared__ double sF[FN][DT_Y][DT_X];        // fields of plane kk filtered along i
+  __shared__ double sU[PART == 0 ? 4 : 1][DT_Y][DT_X];   // u_hat, T_hat of plane kk - 1
+  const int tx = threadIdx.x, ty = threadIdx.y, tid = ty * DT_X + tx;
+  int bx, by, bz;
+  if (!tile_of_block(tm, bx, by, bz)) {        // fills up the last XCD's share
+    if (tid < DY_NSUM && part_sum(PART, tid)) part[(long long)blockIdx.x * DY_NSUM + tid] = 0.0;
+    return;
+  }
+  const int i0 = bx * (DT_X - 2), j0 = by * (DT_Y - 2);
+  const int k0 = bz * kc, k1 = min(k0 + kc, g.nth);
+  const int i = i0 - 1 + tx, j = j0 - 1 + ty;
+  const bool inner = tx >= 1 && tx <= DT_X - 2 && ty >= 1 && ty <= DT_Y - 2 && i < g.nx && j < g.nr;
+  const bool has_b = tid < DT_BORDER;
+  int brx = 0, bry = 0;
+  if (tid < DT_RX) { bry = 0; brx = tid; }
+  else if (tid < 2 * DT_RX) { bry = DT_RY - 1; brx = tid - DT_RX; }
+  else { const int r = tid - 2 * DT_RX; bry = 1 + (r >> 1); brx = (r & 1) ? DT_RX - 1 : 0; }
+  const unsigned oq = q_col<T>(g, i, j), oob = q_col<T>(g, i0 - 2 + brx, j0 - 2 + bry);
+  // filtered state and metrics: columns beyond [-1, n] take the nearest one
+  const int ic = min(max(i, -1), g.nx), jc = min(max(j, -1), g.nr);
+  const unsigned o64 = q_col<double>(g, ic, jc), om = q_col<T>(g, ic, jc);
+  const double* px = PROD ? pt.x + (ic + NG) * PX_N : nullptr;
+  const double xx = PROD ? px[0] : 0.0, rx = PROD ? px[1] : 0.0, d2x = PROD ? px[2] : 0.0;
+  // metric terms, 1 / J^-1 and (d2) |J^-1|^(2/3) of the column at plane k
+  auto metrics = [&](int k, double m[10], double& iV) {
+    if (PROD) {      // the stored terms are those of the storage type
+      const double* t = pt.yz + (long long)(k + NG) * prod_plane(g) + (jc + NG) * PT_N;
+      product_terms(xx, t, m);
+      if (sizeof(T) == 8) {
+        iV = rx * t[6];
+      } else {
+#pragma unroll
+        for (int c = 0; c < 10; ++c) m[c] = (double)(T)m[c];
+        iV = trcp(m[9]);
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < 10; ++c) m[c] = (double)gld(M, g, c, k, om);
+      iV = trcp(m[9]);
+    }
+  };
+
+  double Pm[4], Pc[5], Pp[5];                  // u, v, w, T at kk-1; rho, u, v, w, T at kk, kk+1
+  double uhm[4], uhc[4];                       // u_hat, T_hat at kk-2, kk-1
+  double fa[FN], fb[FN];                       // fields at kk-2 and kk-1, filtered in the plane
+  double S[6], gT[3];                          // resolved strain, temperature gradient at kk-1
+  double acc[DY_NSUM] = {0, 0, 0, 0, 0, 0, 0};
+  {
+    double q[5], p[5];
+    load5(Q, g, oq, k0 - 2, q);
+    prim_t(q, gamma, p);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) Pm[c] = p[1 + c];
+    load5(Q, g, oq, k0 - 1, q);
+    prim_t(q, gamma, Pc);
+    load5(Q, g, oq, k0, q);
+    prim_t(q, gamma, Pp);
+    if (has_b) {
+      double b[5];
+      load5(Q, g, oob, k0 - 1, b);
+      prim_t(b, gamma, p);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sP[c][bry][brx] = p[1 + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) { sP[c][ty + 1][tx + 1] = Pc[1 + c]; uhm[c] = uhc[c] = 0.0; }
+#pragma unroll
+    for (int c = 0; c < FN; ++c) fa[c] = fb[c] = 0.0;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) S[c] = 0.0;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) gT[c] = 0.0;
   }
   __syncthreads();
-  const int IJ[6][2] = {{0, 0}, {1, 1}, {2, 2}, {0, 1}, {0, 2}, {1, 2}};
-  if (kgrad) {
-    for (int e = tid; e < DP_HP; e += DP_X * DP_Y) {
-      const int hx = e % DP_HX, hy = e / DP_HX;
-      const int i = i0 - 1 + hx, j = j0 - 1 + hy;
-      double F[DY_PUU];
-      // only where an interior column's filter reads them
-      if (i >= -1 && i <= g.nx && j >= -1 && j <= g.nr) {
-        const int ep = (hy + 1) * DQ_HX + hx + 1;       // the same point among the primitives
-        const int o = g.at(i, j, k);
-        double dl[3][4];
-        const int sd[2] = {1, DQ_HX};
-        for (int d = 0; d < 2; ++d)
-          for (int f = 0; f < 4; ++f) dl[d][f] = 0.5 * (sP[1 + f][ep + sd[d]] - sP[1 + f][ep - sd[d]]);
-        const PrimD a = prim_at(Q, g, o + g.plane, gamma), b = prim_at(Q, g, o - g.plane, gamma);
-        dl[2][0] = 0.5 * (a.u - b.u);
-        dl[2][1] = 0.5 * (a.v - b.v);
-        dl[2][2] = 0.5 * (a.w - b.w);
-        dl[2][3] = 0.5 * (a.T - b.T);
-        double gu[3][3], gT[3], S[3][3], Smag;
-        chain_rule(dl, M, g, o, gu, gT);
-        strain(gu, S, Smag);
-        const double rho = sP[0][ep], rS = rho * Smag;
-        for (int q = 0; q < 6; ++q) F[DY_FS + q] = rS * S[IJ[q][0]][IJ[q][1]];
-        F[DY_FS2] = rho * Smag * Smag;
-        for (int m = 0; m < 3; ++m) F[DY_FT + m] = rS * gT[m];
-      } else {
-        for (int f = 0; f < DY_PUU; ++f) F[f] = 0.0;
+
+  for (int kk = k0 - 1; kk <= k1; ++kk) {
+    const bool more = kk < k1;
+    // gradients at (i, j, kk)
+    double Sn[6], gTn[3];
+    {
+      double dl[3][4], m[10], iV, gu[4][3], Smag;
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        dl[0][f] = sP[f][ty + 1][tx + 2] - sP[f][ty + 1][tx];
+        dl[1][f] = sP[f][ty + 2][tx + 1] - sP[f][ty][tx + 1];
+        dl[2][f] = Pp[1 + f] - Pm[f];
       }
-      for (int f = 0; f < DY_PUU; ++f) sG[f][e] = F[f];
+      metrics(kk, m, iV);
+      chain_rule<PROD>(dl, m, 0.5 * iV, gu);
+      strain6(gu, Sn, Smag);
+      // field f filtered along i
+      auto put = [&](int f, double v) {
+        sF[f - F0][ty][tx] = filt(from_left<DT_X>(v), v, from_right<DT_X>(v));
+      };
+      const double rho = Pc[0], rS = rho * Smag;
+#pragma unroll
+      for (int x = 0; x < 3; ++x) gTn[x] = gu[3][x];
+      if constexpr (PART == 0) {
+#pragma unroll
+        for (int q = 0; q < 6; ++q) put(DF_S + q, rS * Sn[q]);
+        put(DF_S2, rS * Smag);
+#pragma unroll
+        for (int x = 0; x < 3; ++x) put(DF_T + x, rS * gTn[x]);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sU[c][ty][tx] = uhc[c];
+      } else {
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+          const double ru = rho * Pc[1 + x];
+          put(DF_UU + x, ru * Pc[1 + x]);
+          put(DF_UT + x, ru * Pc[4]);
+        }
+        put(DF_UU + 3, rho * Pc[1] * Pc[2]);
+        put(DF_UU + 4, rho * Pc[1] * Pc[3]);
+        put(DF_UU + 5, rho * Pc[2] * Pc[3]);
+      }
+    }
+    // u_hat, T_hat of plane kk, hats of plane kk-1; own column two planes ahead
+    // and border of the next plane (kk + 2 <= nth + 1 where used)
+    double uhn[4], hn[5], hc[5], qn[5], bn[5];
+    if (PART == 0) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) hn[c] = gld(SC, g, DY_HR + c, kk, o64);
+    }
+#pragma unroll
+    for (int c = 0; c < (PART == 0 ? 1 : 5); ++c) hc[c] = gld(SC, g, DY_HR + c, max(kk - 1, -1), o64);
+    if (more) {
+      load5(Q, g, oq, kk + 2, qn);
+      if (has_b) load5(Q, g, oob, kk + 1, bn);
+    }
+    double du[4];   // their differences along i at plane kk-1 (every lane takes part)
+    if (PART == 0) {
+      const double ihr = trcp(hn[0]);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) uhn[c] = hn[1 + c] * ihr;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) du[c] = from_right<DT_X>(uhc[c]) - from_left<DT_X>(uhc[c]);
+    }
+    __syncthreads();
+    const int tym = max(ty - 1, 0), typ = min(ty + 1, DT_Y - 1);
+    // field f filtered: along j now, along k with the two planes before
+    auto hat = [&](int f) {
+      f -= F0;
+      const double F2 = filt(sF[f][tym][tx], sF[f][ty][tx], sF[f][typ][tx]);
+      const double h = filt(fa[f], fb[f], F2);
+      fa[f] = fb[f];
+      fb[f] = F2;
+      return h;
+    };
+    // terms of the output point (i, j, kk-1), formed by every thread and added
+    // by those that hold one
+    const bool emit = inner && kk > k0;
+    const double trS = S[0] + S[1] + S[2];
+    double m[10], iV;
+    metrics(kk - 1, m, iV);
+    const double V = m[9];
+    if constexpr (PART == 0) {
+      double guh[4][3], Sh[6], dl[3][4], Shmag, ShS = 0.0, gTT = 0.0, D2;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        dl[0][c] = du[c];
+        dl[1][c] = sU[c][typ][tx] - sU[c][tym][tx];
+        dl[2][c] = uhn[c] - uhm[c];
+      }
+      chain_rule<PROD>(dl, m, 0.5 * iV, guh);
+      strain6(guh, Sh, Shmag);
+      const double trSh = Sh[0] + Sh[1] + Sh[2];
+#pragma unroll
+      for (int q = 0; q < 6; ++q) ShS += (q < 3 ? 1.0 : 2.0) * Sh[q] * S[q];
+#pragma unroll
+      for (int x = 0; x < 3; ++x) gTT += guh[3][x] * gT[x];
+      if (PROD && sizeof(T) == 8) {                  // Delta^2 = |J^-1|^(2/3)
+        D2 = d2x * pt.yz[(long long)(kk - 1 + NG) * prod_plane(g) + (jc + NG) * PT_N + 7];
+      } else {
+        const double cV = cbrt(fabs(V));
+        D2 = cV * cV;
+      }
+      const double hrSh = hc[0] * Shmag, Dh2 = 4.0 * D2;
+      double hSS = 0.0, hSmm = 0.0, hTT = 0.0;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const double h = hat(DF_S + q);
+        if (q < 3) hSmm += h;
+        hSS += (q < 3 ? 1.0 : 2.0) * h * S[q];       // symmetric: off-diagonals twice
+      }
+      const double hS2 = hat(DF_S2);
+#pragma unroll
+      for (int x = 0; x < 3; ++x) hTT += hat(DF_T + x) * gT[x];
+      if (emit) {
+        acc[1] += V * (2.0 * Dh2 * hrSh * Shmag - 2.0 * D2 * hS2);              // D_I
+        acc[3] += V * (trS * 2.0 * D2 * hS2 / 3.0);                             // B
+        acc[4] += V * (2.0 * D2 * (hSS - hSmm * trS / 3.0) -
+                       2.0 * Dh2 * hrSh * (ShS - trSh * trS / 3.0));            // D_d
+        acc[5] += V * (D2 * hTT - Dh2 * hrSh * gTT);                            // N_P
+      }
+    } else {
+      const double i_hr = trcp(hc[0]);
+      double Lll = 0.0, LS = 0.0, DP = 0.0;
+      constexpr int IA[6] = {0, 1, 2, 0, 0, 1}, IB[6] = {0, 1, 2, 1, 2, 2};
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const double L = hat(DF_UU + q) - hc[1 + IA[q]] * hc[1 + IB[q]] * i_hr;
+        if (q < 3) Lll += L;
+        LS += (q < 3 ? 1.0 : 2.0) * L * S[q];
+      }
+#pragma unroll
+      for (int x = 0; x < 3; ++x) DP += (hat(DF_UT + x) - hc[1 + x] * hc[4] * i_hr) * gT[x];
+      if (emit) {
+        acc[0] += V * Lll;                                                      // N_I
+        acc[2] += V * (LS - trS * Lll / 3.0);                                   // A
+        acc[6] += V * DP;                                                       // D_P
+      }
+    }
+    // roll the window; plane kk+1 goes to LDS
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      if (PART == 0) { uhm[c] = uhc[c]; uhc[c] = uhn[c]; }
+      Pm[c] = Pc[1 + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 6; ++c) S[c] = Sn[c];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) gT[c] = gTn[c];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) Pc[c] = Pp[c];
+    if (more) {
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sP[c][ty + 1][tx + 1] = Pc[1 + c];
+      prim_t(qn, gamma, Pp);
+      if (has_b) {
+        double p[5];
+        prim_t(bn, gamma, p);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sP[c][bry][brx] = p[1 + c];
+      }
     }
     __syncthreads();
   }
-  const int tx = tid % DP_X, ty = tid / DP_X;
-  const int i = i0 + tx, j = j0 + ty;
-  if (i > g.nx || j > g.nr) return;
-  const int o = g.at(i, j, k);
-  const bool inner_col = i >= 0 && i < g.nx && j >= 0 && j < g.nr && kgrad;
-  // the state fields and the products, formed from the staged primitives
-  // where the filter reads them
-  double acc[DY_NF - DY_PUU];
-  for (int f = 0; f < DY_NF - DY_PUU; ++f) acc[f] = 0.0;
-  for (int b = 0; b < 3; ++b) {
-    double row[DY_NF - DY_PUU];
-    for (int f = 0; f < DY_NF - DY_PUU; ++f) row[f] = 0.0;
-    for (int a = 0; a < 3; ++a) {
-      const int e = (ty + 1 + b) * DQ_HX + tx + 1 + a;
-      const double rho = sP[0][e], uu[3] = {sP[1][e], sP[2][e], sP[3][e]}, Tt = sP[4][e];
-      row[DY_R - DY_PUU] += FW[a] * rho;
-      for (int c = 0; c < 3; ++c) row[DY_R - DY_PUU + 1 + c] += FW[a] * (rho * uu[c]);
-      row[DY_R - DY_PUU + 4] += FW[a] * (rho * Tt);
-      if (inner_col) {
-        for (int q = 0; q < 6; ++q) row[q] += FW[a] * (rho * uu[IJ[q][0]] * uu[IJ[q][1]]);
-        for (int c = 0; c < 3; ++c) row[DY_PUT - DY_PUU + c] += FW[a] * (rho * uu[c] * Tt);
-      }
-    }
-    for (int f = 0; f < DY_NF - DY_PUU; ++f) acc[f] += FW[b] * row[f];
-  }
-  for (int f = inner_col ? DY_PUU : DY_R; f < DY_NF; ++f) SC[(long long)f * g.vs + o] = acc[f - DY_PUU];
-  if (!inner_col) return;
-  for (int f = 0; f < DY_PUU; ++f) {
-    double sum = 0.0;
-    for (int b = 0; b < 3; ++b) {
-      const int e = (ty + b) * DP_HX + tx;
-      sum += FW[b] * (FW[0] * sG[f][e] + FW[1] * sG[f][e + 1] + FW[2] * sG[f][e + 2]);
-    }
-    SC[(long long)f * g.vs + o] = sum;
-  }
-}
 
-// hat(rho), hat(rho u_i), hat(rho T) at the points of [-1, n]^3: the
-// i-j-filtered fields filtered along k.  One thread per element of the rows
-// j in [-1, n] of the planes [-1, n] (whole rows, so stores fill lines).
-__global__ __launch_bounds__(DY_BS) void k_dyn_hat(Grid g, double* __restrict__ SC) {
-  const long long rows = (long long)(g.nr + 2) * (g.nth + 2);
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (t >= rows * g.pitch) return;
-  const int i = (int)(t % g.pitch) - NG;
-  const long long r = t / g.pitch;
-  const int j = (int)(r % (g.nr + 2)) - 1, k = (int)(r / (g.nr + 2)) - 1;
-  if (i < -1 || i > g.nx) return;
-  const int o = g.at(i, j, k);
-  for (int f = 0; f < 5; ++f) {
-    const double* F = SC + (long long)(DY_R + f) * g.vs;
-    SC[(long long)(DY_HR + f) * g.vs + o] =
-        FW[0] * F[o - g.plane] + FW[1] * F[o] + FW[2] * F[o + g.plane];
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(DY_BS) void k_dyn_sums(const T* __restrict__ Q,
-                                                    const T* __restrict__ M, Grid g,
-                                                    double gamma, const double* __restrict__ SC,
-                                                    double* __restrict__ part) {
-  __shared__ double red[DY_NSUM][DY_BS];
-  // blocks of an interior plane dealt to the eight XCDs so that each XCD
-  // walks its share of every plane in order (the k-neighbour planes are then
-  // in its own L2)
-  const int P = (g.nx * g.nr + DY_BS - 1) / DY_BS, Pmax = (P + DY_NXCD - 1) / DY_NXCD;
-  const int hw = blockIdx.x, x = hw % DY_NXCD, r = hw / DY_NXCD;
-  const int k = r / Pmax, pb = x * Pmax + r % Pmax;
-  const int q0 = pb * DY_BS + (int)threadIdx.x;
-  double term[DY_NSUM] = {0, 0, 0, 0, 0, 0, 0};
-  if (k < g.nth && pb < P && q0 < g.nx * g.nr) {
-    const int i = q0 % g.nx, j = q0 / g.nx;
-    const int o = g.at(i, j, k);
-    // resolved strain and temperature gradient at the point
-    double gu[3][3], gT[3], S[3][3], Smag;
-    gradients(Q, M, g, o, gamma, gu, gT);
-    strain(gu, S, Smag);
-    const double trS = S[0][0] + S[1][1] + S[2][2];
-    // the other filtered fields: the i-j-filtered ones filtered along k
-    double hF[DY_PUU], hP[DY_NG - DY_PUU];
-    for (int f = 0; f < DY_NG; ++f) {
-      const double* F = SC + (long long)f * g.vs;
-      const double v = FW[0] * F[o - g.plane] + FW[1] * F[o] + FW[2] * F[o + g.plane];
-      if (f < DY_PUU) hF[f] = v; else hP[f - DY_PUU] = v;
-    }
-    const double hr = SC[(long long)DY_HR * g.vs + o];
-    const double ihr = trcp(hr);
-    double hru[3];
-    for (int c = 0; c < 3; ++c) hru[c] = SC[(long long)(DY_HRU + c) * g.vs + o];
-    const double hrT = SC[(long long)DY_HRT * g.vs + o];
-    // strain of u_hat and gradient of T_hat (central differences of the
-    // filtered fields at the neighbours, metrics of the point)
-    const int step[3] = {1, g.pitch, g.plane};
-    double dl[3][4];
-    for (int d = 0; d < 3; ++d) {
-      const int op = o + step[d], om = o - step[d];
-      const double irp = trcp(SC[(long long)DY_HR * g.vs + op]);
-      const double irm = trcp(SC[(long long)DY_HR * g.vs + om]);
-      for (int c = 0; c < 3; ++c)
-        dl[d][c] = 0.5 * (SC[(long long)(DY_HRU + c) * g.vs + op] * irp -
-                          SC[(long long)(DY_HRU + c) * g.vs + om] * irm);
-      dl[d][3] = 0.5 * (SC[(long long)DY_HRT * g.vs + op] * irp - SC[(long long)DY_HRT * g.vs + om] * irm);
-    }
-    const double V = (double)M[9LL * g.vs + o];
-    const double iV = trcp(V);
-    double guh[3][3], gTh[3];
-    for (int m = 0; m < 3; ++m) {
-      const double S0 = (double)M[(long long)m * g.vs + o];
-      const double S1 = (double)M[(long long)(3 + m) * g.vs + o];
-      const double S2 = (double)M[(long long)(6 + m) * g.vs + o];
-      for (int f = 0; f < 3; ++f) guh[f][m] = (S0 * dl[0][f] + S1 * dl[1][f] + S2 * dl[2][f]) * iV;
-      gTh[m] = (S0 * dl[0][3] + S1 * dl[1][3] + S2 * dl[2][3]) * iV;
-    }
-    double Sh[3][3], Shmag;
-    strain(guh, Sh, Shmag);
-    const double trSh = Sh[0][0] + Sh[1][1] + Sh[2][2];
-    const double cV = cbrt(fabs(V));
-    const double D2 = cV * cV;                       // Delta^2 = |J^-1|^(2/3)
-    const double Dh2 = 4.0 * D2;
-    // L_ij and the contractions
-    const int IJ[6][2] = {{0, 0}, {1, 1}, {2, 2}, {0, 1}, {0, 2}, {1, 2}};
-    double Lll = 0.0, LS = 0.0, hSS = 0.0, ShS = 0.0;
-    for (int q = 0; q < 6; ++q) {
-      const int a = IJ[q][0], b = IJ[q][1];
-      const double w = a == b ? 1.0 : 2.0;            // symmetric: off-diagonals twice
-      const double L = hP[q] - hru[a] * hru[b] * ihr;
-      if (a == b) Lll += L;
-      LS += w * L * S[a][b];
-      hSS += w * hF[DY_FS + q] * S[a][b];
-      ShS += w * Sh[a][b] * S[a][b];
-    }
-    const double hSmm = hF[DY_FS + 0] + hF[DY_FS + 1] + hF[DY_FS + 2];
-    const double hS2 = hF[DY_FS2];
-    double NP = 0.0, DP = 0.0;
-    for (int m = 0; m < 3; ++m) {
-      NP += D2 * hF[DY_FT + m] * gT[m] - Dh2 * hr * Shmag * gTh[m] * gT[m];
-      DP += (hP[6 + m] - hru[m] * hrT * ihr) * gT[m];
-    }
-    term[0] = Lll;                                                     // N_I
-    term[1] = 2.0 * Dh2 * hr * Shmag * Shmag - 2.0 * D2 * hS2;         // D_I
-    term[2] = LS - trS * Lll / 3.0;                                    // A
-    term[3] = trS * 2.0 * D2 * hS2 / 3.0;                              // B
-    term[4] = 2.0 * D2 * (hSS - hSmm * trS / 3.0) -
-              2.0 * Dh2 * (hr * Shmag * ShS - hr * Shmag * trSh * trS / 3.0);   // D_d
-    term[5] = NP;
-    term[6] = DP;
-    for (int q = 0; q < DY_NSUM; ++q) term[q] *= V;
-  }
-  for (int q = 0; q < DY_NSUM; ++q) red[q][threadIdx.x] = term[q];
+  double* red = &sF[0][0][0];
+  for (int q = 0; q < DY_NSUM; ++q) red[q * DY_BS + tid] = acc[q];
   __syncthreads();
   for (int w = DY_BS / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w)
-      for (int q = 0; q < DY_NSUM; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + w];
+    if (tid < w)
+      for (int q = 0; q < DY_NSUM; ++q) red[q * DY_BS + tid] += red[q * DY_BS + tid + w];
     __syncthreads();
   }
-  if (threadIdx.x < DY_NSUM) part[(long long)blockIdx.x * DY_NSUM + threadIdx.x] = red[threadIdx.x][0];
+  if (tid < DY_NSUM && part_sum(PART, tid)) part[(long long)blockIdx.x * DY_NSUM + tid] = red[tid * DY_BS];
 }
 
 // dyn[0] = C_ds+ / Cv (eddy-viscosity coefficient in jet-viscosity units),
@@ -375,32 +467,54 @@ __global__ __launch_bounds__(DY_BS) void k_dyn_final(const double* __restrict__ 
   for (int q = 0; q < DY_NSUM; ++q) dyn[6 + q] = red[q][0];
 }
 
-int dyn_blocks(const Grid& g) {
-  const int P = (g.nx * g.nr + DY_BS - 1) / DY_BS;
-  return DY_NXCD * ((P + DY_NXCD - 1) / DY_NXCD) * g.nth;
+static int dyn_terms_map(const Grid& g, int num_cu, TileMap& tm) {
+  const int gx = (g.nx + DT_X - 3) / (DT_X - 2), gy = (g.nr + DT_Y - 3) / (DT_Y - 2);
+  const int kc = dyn_chunk((long long)gx * gy, g.nth, 2 * num_cu, 3);
+  tm = tile_map(gx, gy, (g.nth + kc - 1) / kc);
+  return kc;
+}
+
+int dyn_blocks(const Grid& g, int num_cu) {
+  TileMap tm;
+  dyn_terms_map(g, num_cu, tm);
+  return tm.per_xcd * NXCD;
 }
 
 template <typename T>
 hipError_t launch_dynamic(const T* Q, const T* M, const Grid& g, double gamma, double Cv,
-                          double Pr_static, double* SC, double* part, double* dyn,
-                          hipStream_t s) {
-  const int tiles_x = (g.nx + 3 + DP_X - 1) / DP_X, tiles_y = (g.nr + 2 + DP_Y - 1) / DP_Y;
-  hipLaunchKernelGGL(k_dyn_plane<T>, dim3(tiles_x * tiles_y, g.nth + 2 * NG), dim3(DP_X * DP_Y), 0, s,
-                     Q, M, g, gamma, tiles_x, SC);
-  const long long nrow = (long long)(g.nr + 2) * (g.nth + 2) * g.pitch;
-  hipLaunchKernelGGL(k_dyn_hat, dim3(blocks_for(nrow, DY_BS)), dim3(DY_BS), 0, s, g, SC);
-  const int nb = dyn_blocks(g);
-  hipLaunchKernelGGL(k_dyn_sums<T>, dim3(nb), dim3(DY_BS), 0, s, Q, M, g, gamma,
-                     (const double*)SC, part);
+                          double Pr_static, double* SC, double* part, double* dyn, int num_cu,
+                          const ProdTab& pt, hipStream_t s) {
+  {
+    const int gx = (g.nx + 2 + DH_X - 3) / (DH_X - 2), gy = (g.nr + 2 + DH_Y - 1) / DH_Y;
+    const int kc = dyn_chunk((long long)gx * gy, g.nth + 2, 8 * num_cu, 3);
+    const TileMap tm = tile_map(gx, gy, (g.nth + 2 + kc - 1) / kc);
+    hipLaunchKernelGGL(k_dyn_hat<T>, dim3(tm.per_xcd * NXCD), dim3(DH_X, DH_Y), 0, s, Q, g, gamma, kc,
+                       tm, SC);
+  }
+  TileMap tm;
+  const int kc = dyn_terms_map(g, num_cu, tm);
+  const int nb = tm.per_xcd * NXCD;
+#define LESJET_DYN_TERMS(P, PART)                                                               \
+  hipLaunchKernelGGL((k_dyn_terms<T, P, PART>), dim3(nb), dim3(DT_X, DT_Y), 0, s, Q, M, g, gamma, \
+                     kc, tm, pt, (const double*)SC, part)
+  if (pt.x) {
+    LESJET_DYN_TERMS(true, 0);
+    LESJET_DYN_TERMS(true, 1);
+  } else {
+    LESJET_DYN_TERMS(false, 0);
+    LESJET_DYN_TERMS(false, 1);
+  }
+#undef LESJET_DYN_TERMS
   hipLaunchKernelGGL(k_dyn_final, dim3(1), dim3(DY_BS), 0, s, (const double*)part, nb, Cv,
                      Pr_static, dyn);
   return hipGetLastError();
 }
 
 template hipError_t launch_dynamic<double>(const double*, const double*, const Grid&, double,
-                                           double, double, double*, double*, double*,
-                                           hipStream_t);
+                                           double, double, double*, double*, double*, int,
+                                           const ProdTab&, hipStream_t);
 template hipError_t launch_dynamic<float>(const float*, const float*, const Grid&, double, double,
-                                          double, double*, double*, double*, hipStream_t);
+                                          double, double*, double*, double*, int, const ProdTab&,
+                                          hipStream_t);
 
 }  // namespace lesjet

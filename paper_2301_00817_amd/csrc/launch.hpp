@@ -56,15 +56,15 @@ hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph
 
 // Dynamic Smagorinsky coefficients of the ghost-filled state Q: scratch SC
 // (DYN_SCRATCH_VARS padded FP64 variables), part (7 doubles per block of
-// dyn_blocks(g)), dyn (DYN_COEF_DOUBLES): [0] C_ds+ / Cv, [1] 1 / Pr_sgs,
+// dyn_blocks), dyn (DYN_COEF_DOUBLES): [0] C_ds+ / Cv, [1] 1 / Pr_sgs,
 // [2] (2/3) C_I+, [3..5] C_I, C_ds, Pr_sgs as computed, [6..12] the sums.
-constexpr int DYN_SCRATCH_VARS = 29;
+constexpr int DYN_SCRATCH_VARS = 5;
 constexpr int DYN_COEF_DOUBLES = 16;
-int dyn_blocks(const Grid& g);
+int dyn_blocks(const Grid& g, int num_cu);
 template <typename T>
 hipError_t launch_dynamic(const T* Q, const T* M, const Grid& g, double gamma, double Cv,
-                          double Pr_static, double* SC, double* part, double* dyn,
-                          hipStream_t s);
+                          double Pr_static, double* SC, double* part, double* dyn, int num_cu,
+                          const ProdTab& pt, hipStream_t s);
 
 enum { FUSED_EPI_R = 0, FUSED_EPI_RK = 1, FUSED_EPI_RK_LAST = 2 };
 // viscosity schedule of the stage kernel (same values as LAG_* of the
