@@ -108,11 +108,13 @@ __device__ __forceinline__ bool plane_block(const Grid& g, PlaneMap pm, int& kk,
 // are formed once into LDS for the sensors' xi and eta neighbours.
 constexpr int PT_X = 32, PT_Y = 8, PT_HX = PT_X + 2, PT_HP = PT_HX * (PT_Y + 2);
 
+template <bool PROD>
 __global__ __launch_bounds__(PT_X * PT_Y) void k_adj_prep(const double* __restrict__ Q,
                                                           const double* __restrict__ M, Grid g,
-                                                          Phys<double> ph, PlaneMap pm,
+                                                          Phys<double> ph, ProdTab pt, PlaneMap pm,
                                                           int tiles_x, double* __restrict__ SC) {
   __shared__ double sp[PT_HP];
+  __shared__ __align__(16) double sT[PROD ? PT_Y : 1][PT_N];   // product mesh: the tile's table rows
   int kk, pb;
   if (!plane_block(g, pm, kk, pb)) return;   // uniform over the block
   const int i0 = (pb % tiles_x) * PT_X - NG, j0 = (pb / tiles_x) * PT_Y - NG, k = kk - NG;
@@ -128,6 +130,10 @@ __global__ __launch_bounds__(PT_X * PT_Y) void k_adj_prep(const double* __restri
   if (r1) {
     load5d(Q, g, o - g.plane, qm);
     load5d(Q, g, o + g.plane, qp);
+  }
+  if (PROD && threadIdx.x < PT_Y * PT_N) {
+    const int r = threadIdx.x / PT_N, c = threadIdx.x % PT_N, jr = min(j0 + r, g.nr + NG - 1);
+    sT[r][c] = pt.yz[(long long)kk * prod_plane(g) + (jr + NG) * PT_N + c];
   }
   for (int e = threadIdx.x; e < PT_HP; e += PT_X * PT_Y) {
     // clamped to the padded box: a clamped slot feeds no stored value
@@ -149,22 +155,33 @@ __global__ __launch_bounds__(PT_X * PT_Y) void k_adj_prep(const double* __restri
       SC[(long long)(S_LB + d) * g.vs + o] = 0.0;
       SC[(long long)(S_NU + d) * g.vs + o] = 0.0;
     }
-    SC[(long long)S_IV * g.vs + o] = 0.0;
+    if (!PROD) SC[(long long)S_IV * g.vs + o] = 0.0;
     return;
   }
   // J^-1 = 0 on the axis row of a centerline-through-the-nodes mesh: no face
   // uses its lambda_bar and its Rbar is ignored, so 0 is stored there
   const bool axis_row = ph.axis_node && j == 0;
-  const double iV = axis_row ? 0.0 : trcp(M[9LL * g.vs + o]);
-  SC[(long long)S_IV * g.vs + o] = iV;
+  double m[10], len[3], iV;
+  if (PROD) {
+    const double* px = pt.x + (i + NG) * PX_N;
+    const double xx = px[0];
+    product_terms(xx, sT[ty], m);
+    iV = axis_row ? 0.0 : px[1] * sT[ty][6];
+    len[0] = fabs(m[0]);
+    len[1] = fabs(xx) * sT[ty][4];
+    len[2] = fabs(xx) * sT[ty][5];
+  } else {
+    for (int c = 0; c < 10; ++c) m[c] = M[(long long)c * g.vs + o];
+    iV = axis_row ? 0.0 : trcp(m[9]);
+    SC[(long long)S_IV * g.vs + o] = iV;
+    for (int d = 0; d < 3; ++d) len[d] = row_norm<false>(d, m + 3 * d);
+  }
   const double a = tsqrt(pr[3]);
   const double aiV = fabs(iV);
   double lam[3];
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const double S0 = M[(long long)(3 * d) * g.vs + o], S1 = M[(long long)(3 * d + 1) * g.vs + o],
-                 S2 = M[(long long)(3 * d + 2) * g.vs + o];
-    const double Uc = S0 * pr[0] + S1 * pr[1] + S2 * pr[2];
-    lam[d] = (fabs(Uc) + a * tsqrt(S0 * S0 + S1 * S1 + S2 * S2)) * aiV;
+    lam[d] = (fabs(row_dot<PROD>(d, m + 3 * d, pr[0], pr[1], pr[2])) + a * len[d]) * aiV;
     double pl, pu;
     if (d < 2) {                       // in the plane: from LDS
       const int sd = d == 0 ? 1 : PT_HX;
@@ -266,16 +283,22 @@ __device__ __forceinline__ void face_self_axis(const FaceCoef& f, const double* 
 // Rbar / J^-1 is zero off the interior (and on the axis row of a
 // centerline-through-the-nodes mesh, where R = 0); W = (rho, rho u, rho v,
 // rho w, E + p).
+template <bool PROD>
 struct ZetaLine {
   const double (*zc)[9];
   const double (*zw)[6];
+  const double (*sA)[2];   // product mesh: (A, 1 / A) of line point m at sA[m * stride]
+  int stride;
+  double xx, rx;           // and x_xi, 1 / x_xi
+  double f;                // factor of Rbar
   bool row_inner;
   int s, n;
   __device__ __forceinline__ void coef(int m, double rt[5], double& lb, double& nu, double& v) const {
     const int k = min(max(s + m - 2, -NG), n - 1 + NG);
     const bool inner = row_inner && k >= 0 && k < n;
-    v = zc[m][0];
-    for (int q = 0; q < 5; ++q) rt[q] = inner ? zc[m][2 + q] * zc[m][1] : 0.0;
+    v = PROD ? xx * sA[m * stride][0] : zc[m][0];
+    const double iV = PROD ? rx * sA[m * stride][1] : zc[m][1];
+    for (int q = 0; q < 5; ++q) rt[q] = inner ? f * zc[m][2 + q] * iV : 0.0;
     lb = zc[m][7];
     nu = zc[m][8];
   }
@@ -333,12 +356,13 @@ __device__ __forceinline__ void dir_part(const Line& ln, int s, int d, int n, co
 // and whose other outputs are unused since J^-1 = 0 there), the sensor
 // reverse and the writes of S_NC, S_DL; for every p the reverse of the
 // primitives -> S_PQ.
-template <class Prim>
+// sT, xx: product mesh, the point's table row and x values (pt.x)
+template <bool PROD, class Prim>
 __device__ __forceinline__ void point_part(const double* __restrict__ M, double* __restrict__ SC,
                                            const Grid& g, int o, bool r1,
                                            bool axis_row, const Phys<double>& ph, const Prim& pv,
                                            const double gb[3][5], double lbb[3], const double nub[3],
-                                           const double wb[5]) {
+                                           const double wb[5], const double* sT, const double* px) {
   double q[5];
   pv.state(q);
   double qb[5], prb[5] = {0, 0, 0, 0, 0};
@@ -359,11 +383,25 @@ __device__ __forceinline__ void point_part(const double* __restrict__ M, double*
       in.nu[d] = 0.0;                        // not used by the reverse
       pm[d] = m[4];
       pp[d] = pl[4];
-      for (int c = 0; c < 3; ++c) in.S[d][c] = M[(long long)(3 * d + c) * g.vs + o];
+      if (!PROD)
+        for (int c = 0; c < 3; ++c) in.S[d][c] = M[(long long)(3 * d + c) * g.vs + o];
+    }
+    if (PROD) {
+      double m[10];
+      product_terms(px[0], sT, m);
+#pragma unroll
+      for (int d = 0; d < 3; ++d)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) in.S[d][c] = m[3 * d + c];
+      in.iV = px[1] * sT[6];
+      in.len[0] = fabs(m[0]);
+      in.len[1] = fabs(px[0]) * sT[4];
+      in.len[2] = fabs(px[0]) * sT[5];
+      in.d2 = px[2] * sT[7];
     }
     in.V = pv.vol();
     PointBar<double> bar = {};
-    if (!axis_row) point_quantities_vjp(in, ph, gb, lbb, bar);
+    if (!axis_row) point_quantities_vjp<PROD>(in, ph, gb, lbb, bar);
     for (int d = 0; d < 3; ++d) {
       double side, centre;
       sensor_vjp(pm[d], in.pr[4], pp[d], nub[d], side, centre);
@@ -439,12 +477,19 @@ struct LdsPoint {
   __device__ __forceinline__ double vol() const { return sh[L_V * AT_HP + slot]; }
 };
 
+// fr: factor of Rbar.  PROD: product mesh; its J^-1, reciprocals and metric terms
+// come from the tables, staged in LDS (the tile's rows at the five planes of
+// the zeta lines), which spares 22 of the 140 loads of a point; with the same in
+// the prep pass (105 -> 72 us) the VJP fell from 0.645 to 0.591 ms.
+template <bool PROD>
 __global__ __launch_bounds__(256) void k_adj_main(const double* __restrict__ Q,
                                                   const double* __restrict__ M, Grid g,
-                                                  Phys<double> ph, PlaneMap pm, int tiles_x,
-                                                  const double* __restrict__ Rb,
-                                                  double* __restrict__ SC) {
+                                                  Phys<double> ph, ProdTab pt, PlaneMap pm,
+                                                  int tiles_x, const double* __restrict__ Rb,
+                                                  double fr, double* __restrict__ SC) {
   __shared__ double sh[L_N * AT_HP];
+  __shared__ double sA[PROD ? 5 * AT_HY : 1][2];               // A, 1 / A of rows j0-2 .., planes k-2 ..
+  __shared__ __align__(16) double sT[PROD ? AT_Y : 1][PT_N];   // table rows j0 .. at plane k
   int kk, pb;
   if (!plane_block(g, pm, kk, pb)) return;   // uniform over the block
   const int i0 = (pb % tiles_x) * AT_X - NG, j0 = (pb / tiles_x) * AT_Y - NG, k = kk - NG;
@@ -453,6 +498,53 @@ __global__ __launch_bounds__(256) void k_adj_main(const double* __restrict__ Q,
   const bool live = pos[0] < g.nx + NG && pos[1] < g.nr + NG;
   // zeta faces exist where (i, j) is interior
   const bool zeta = live && pos[0] >= 0 && pos[0] < g.nx && pos[1] >= 0 && pos[1] < g.nr;
+  // table values to stage: loaded first, as everything behind them is loaded
+  // in order
+  const int tt = threadIdx.x;
+  const bool has_t = PROD && tt >= 64 && tt < 64 + AT_Y * PT_N;
+  double ty5[5] = {0, 0, 0, 0, 0};
+  if (PROD && tt < 5 * AT_HY) {
+    const int jr = min(max(j0 - 2 + tt % AT_HY, -NG), g.nr + NG - 1);
+    const int kr = min(max(k - 2 + tt / AT_HY, -NG), g.nth + NG - 1);
+    const double* y = pt.yz + (long long)(kr + NG) * prod_plane(g) + (jr + NG) * PT_N;
+    for (int c = 0; c < 4; ++c) ty5[c] = y[c];
+    ty5[4] = y[6];
+  } else if (has_t) {
+    const int jr = min(j0 + (tt - 64) / PT_N, g.nr + NG - 1);
+    ty5[0] = pt.yz[(long long)kk * prod_plane(g) + (jr + NG) * PT_N + tt % PT_N];
+  }
+  // The values of the thread's one or two staged slots, both sets of loads
+  // ahead of the zeta line's: loads return in order, so the staging waits for
+  // its own only (one slot after the other behind the zeta line, the VJP took
+  // 4 % longer: 0.591 against 0.566 ms on 2.05 M points).
+  struct Staged { double q[5], rb[5], lb[2], nu[2], v, iv; };
+  auto fetch = [&](Staged& st, int e) {
+    const int i = min(max(i0 + e % AT_HX - 2, -NG), g.nx - 1 + NG);
+    const int j = min(max(j0 + e / AT_HX - 2, -NG), g.nr - 1 + NG);
+    const int oe = g.at(i, j, k);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      st.q[c] = Q[(long long)c * g.vs + oe];
+      st.rb[c] = Rb[(long long)c * g.vs + oe];
+    }
+#pragma unroll
+    for (int d = 0; d < 2; ++d) {
+      st.lb[d] = SC[(long long)(S_LB + d) * g.vs + oe];
+      st.nu[d] = SC[(long long)(S_NU + d) * g.vs + oe];
+    }
+    if (PROD) {
+      st.v = pt.x[(i + NG) * PX_N];
+      st.iv = pt.x[(i + NG) * PX_N + 1];
+    } else {
+      st.v = M[9LL * g.vs + oe];
+      st.iv = SC[(long long)S_IV * g.vs + oe];
+    }
+  };
+  static_assert(AT_HP <= 512 && AT_HP > 256, "one or two slots per thread");
+  const bool two = threadIdx.x + 256 < AT_HP;
+  Staged s0, s1;
+  fetch(s0, threadIdx.x);
+  if (two) fetch(s1, threadIdx.x + 256);
   // the zeta line's values, loaded ahead of the staging so that both sets
   // of loads are in flight together (0.72 -> 0.655 ms per VJP on 2.05 M
   // points against loading them after the staging)
@@ -461,8 +553,10 @@ __global__ __launch_bounds__(256) void k_adj_main(const double* __restrict__ Q,
     const int o = g.at(pos[0], pos[1], pos[2]);
     for (int m = 0; m < 5; ++m) {
       const int om = o + (min(max(k + m - 2, -NG), g.nth - 1 + NG) - k) * g.plane;
-      zc[m][0] = M[9LL * g.vs + om];
-      zc[m][1] = SC[(long long)S_IV * g.vs + om];
+      if (!PROD) {
+        zc[m][0] = M[9LL * g.vs + om];
+        zc[m][1] = SC[(long long)S_IV * g.vs + om];
+      }
       for (int c = 0; c < 5; ++c) zc[m][2 + c] = Rb[(long long)c * g.vs + om];
       zc[m][7] = SC[(long long)(S_LB + 2) * g.vs + om];
       zc[m][8] = SC[(long long)(S_NU + 2) * g.vs + om];
@@ -470,38 +564,52 @@ __global__ __launch_bounds__(256) void k_adj_main(const double* __restrict__ Q,
       zw[m][5] = SC[(long long)S_P * g.vs + om];
     }
   }
-  for (int e = threadIdx.x; e < AT_HP; e += 256) {
+  if (PROD) {
+    if (tt < 5 * AT_HY) {
+      sA[tt][0] = ty5[0] * ty5[3] - ty5[2] * ty5[1];
+      sA[tt][1] = ty5[4];
+    } else if (has_t) {
+      sT[(tt - 64) / PT_N][tt % PT_N] = ty5[0];
+    }
+    __syncthreads();
+  }
+  auto stage = [&](const Staged& st, int e) {
     const int i = min(max(i0 + e % AT_HX - 2, -NG), g.nx - 1 + NG);
     const int j = min(max(j0 + e / AT_HX - 2, -NG), g.nr - 1 + NG);
-    const int oe = g.at(i, j, k);
-    double q[5], pr[5];
-    load5d(Q, g, oe, q);
-    prim5(q, ph, pr);
-    const double V = M[9LL * g.vs + oe], iV = SC[(long long)S_IV * g.vs + oe];
+    double pr[5];
+    prim5(st.q, ph, pr);
+    const double V = PROD ? st.v * sA[2 * AT_HY + e / AT_HX][0] : st.v;
+    const double iV = PROD ? st.iv * sA[2 * AT_HY + e / AT_HX][1] : st.iv;
     // R has no entries off the interior nor on a centerline row
     const bool inner = interior(g, i, j, k) && !(ph.axis_node && j == 0);
+#pragma unroll
     for (int c = 0; c < 5; ++c) {
-      sh[(L_RT + c) * AT_HP + e] = inner ? Rb[(long long)c * g.vs + oe] * iV : 0.0;
-      sh[(L_Q + c) * AT_HP + e] = q[c];
+      sh[(L_RT + c) * AT_HP + e] = inner ? fr * st.rb[c] * iV : 0.0;
+      sh[(L_Q + c) * AT_HP + e] = st.q[c];
       sh[(L_PR + c) * AT_HP + e] = pr[c];
     }
+#pragma unroll
     for (int d = 0; d < 2; ++d) {
-      sh[(L_LB + d) * AT_HP + e] = SC[(long long)(S_LB + d) * g.vs + oe];
-      sh[(L_NU + d) * AT_HP + e] = SC[(long long)(S_NU + d) * g.vs + oe];
+      sh[(L_LB + d) * AT_HP + e] = st.lb[d];
+      sh[(L_NU + d) * AT_HP + e] = st.nu[d];
     }
     sh[L_V * AT_HP + e] = V;
-  }
+  };
+  stage(s0, threadIdx.x);
+  if (two) stage(s1, threadIdx.x + 256);
   __syncthreads();
   if (!live) return;
   const int slot = (ty + 2) * AT_HX + tx + 2;
   const int nn[3] = {g.nx, g.nr, g.nth};
   const int o = g.at(pos[0], pos[1], pos[2]);
   const bool r1 = in_r1(g, pos[0], pos[1], pos[2]);
+  const double* px = PROD ? pt.x + (pos[0] + NG) * PX_N : nullptr;
   double gb[3][5], lbb[3] = {0, 0, 0}, nub[3] = {0, 0, 0}, wb[5] = {0, 0, 0, 0, 0};
   for (int d = 0; d < 3; ++d)
     for (int c = 0; c < 5; ++c) gb[d][c] = 0.0;
   if (zeta) {
-    const ZetaLine ln = {zc, zw, !(ph.axis_node && pos[1] == 0), pos[2], g.nth};
+    const ZetaLine<PROD> ln = {zc, zw, sA + (PROD ? ty + 2 : 0), AT_HY, PROD ? px[0] : 0.0,
+                               PROD ? px[1] : 0.0, fr, !(ph.axis_node && pos[1] == 0), pos[2], g.nth};
     dir_part(ln, pos[2], 2, g.nth, ph, wb, gb[2], lbb[2], nub[2]);
   }
   for (int d = 0; d < 2; ++d) {
@@ -513,7 +621,8 @@ __global__ __launch_bounds__(256) void k_adj_main(const double* __restrict__ Q,
     dir_part(ln, pos[d], d, nn[d], ph, wb, gb[d], lbb[d], nub[d]);
   }
   const LdsPoint pv = {sh, Q, &ph, slot, g.vs, o, g.plane};
-  point_part(M, SC, g, o, r1, ph.axis_node && pos[1] == 0, ph, pv, gb, lbb, nub, wb);
+  point_part<PROD>(M, SC, g, o, r1, ph.axis_node && pos[1] == 0, ph, pv, gb, lbb, nub, wb,
+                   sT[PROD ? ty : 0], px);
 }
 
 // Pass 3: cotangent of the padded state = own part + the neighbours'
@@ -776,17 +885,26 @@ hipError_t launch_centerline_transpose(double* Qb, const Grid& g, hipStream_t s)
 }
 
 // Element-wise kernels of the RK5-step adjoint.  x and y may be the same
-// array (the step adjoint scales a cotangent in place, and Qbar_n may alias
-// Qbar_np1): each thread reads its element before writing it and touches no
-// other, so the pointers carry no __restrict__.
-__global__ void k_scale(const double* x, double a, double* y, long long n) {
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (t < n) y[t] = a * x[t];
-}
+// array (Qbar_n may alias Qbar_np1): each thread reads its element before
+// writing it and touches no other, so the pointers carry no __restrict__.
 
-__global__ void k_accumulate(const double* __restrict__ x, double* __restrict__ y, long long n) {
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (t < n) y[t] += x[t];
+// y = ((((x + b0) + b1) + b2) + b3) + b4 with x taken on the interior only (the b
+// are zero elsewhere): the step adjoint's sum, in one pass of seven arrays.
+// (An interior copy, five accumulations and five scalings, now a factor of
+// the residual adjoint, moved 27 arrays: 0.42 ms of a 4.2 ms step adjoint on
+// 2.05 M points.)
+__global__ void k_step_sum(const double* x, const double* __restrict__ b0,
+                           const double* __restrict__ b1, const double* __restrict__ b2,
+                           const double* __restrict__ b3, const double* __restrict__ b4, double* y,
+                           Grid g) {
+  const int o = blockIdx.x * 256 + (int)threadIdx.x;
+  if (o >= g.vs) return;
+  const int k = o / g.plane, r = o - k * g.plane, j = r / g.pitch, i = r - j * g.pitch;
+  const bool in = interior(g, i - NG, j - NG, k - NG);
+  for (int c = 0; c < 5; ++c) {
+    const long long t = (long long)c * g.vs + o;
+    y[t] = in ? ((((x[t] + b0[t]) + b1[t]) + b2[t]) + b3[t]) + b4[t] : 0.0;
+  }
 }
 
 // y = x on the interior, 0 on ghosts and pitch padding (5 variables); x and
@@ -804,28 +922,34 @@ hipError_t launch_interior_copy(const double* x, double* y, const Grid& g, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_scale(const double* x, double a, double* y, long long n, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale, dim3(blocks_for(n, 256)), dim3(256), 0, s, x, a, y, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_accumulate(const double* x, double* y, long long n, hipStream_t s) {
-  hipLaunchKernelGGL(k_accumulate, dim3(blocks_for(n, 256)), dim3(256), 0, s, x, y, n);
+hipError_t launch_step_sum(const double* x, const double* const b[5], double* y, const Grid& g,
+                           hipStream_t s) {
+  hipLaunchKernelGGL(k_step_sum, dim3(blocks_for(g.vs, 256)), dim3(256), 0, s, x, b[0], b[1], b[2], b[3],
+                     b[4], y, g);
   return hipGetLastError();
 }
 
 hipError_t launch_residual_vjp(const double* Q, const double* M, const Grid& g,
                                const Phys<double>& ph, const int bc[6], const double ref_prim[5],
-                               double p_exit, const double* inflow, const double* Rb, double* SC,
-                               double* Qb, double* inflow_bar, hipStream_t s) {
+                               double p_exit, const double* inflow, const double* Rb, double fr,
+                               double* SC, double* Qb, double* inflow_bar, const ProdTab& pt,
+                               hipStream_t s) {
   const int ptiles_x = (g.nx + 2 * NG + PT_X - 1) / PT_X;
   const PlaneMap ppm = plane_map(ptiles_x * ((g.nr + 2 * NG + PT_Y - 1) / PT_Y));
-  hipLaunchKernelGGL(k_adj_prep, dim3(plane_map_grid(ppm, g)), dim3(PT_X * PT_Y), 0, s, Q, M, g, ph,
-                     ppm, ptiles_x, SC);
+  if (pt.x)
+    hipLaunchKernelGGL(k_adj_prep<true>, dim3(plane_map_grid(ppm, g)), dim3(PT_X * PT_Y), 0, s, Q, M,
+                       g, ph, pt, ppm, ptiles_x, SC);
+  else
+    hipLaunchKernelGGL(k_adj_prep<false>, dim3(plane_map_grid(ppm, g)), dim3(PT_X * PT_Y), 0, s, Q, M,
+                       g, ph, pt, ppm, ptiles_x, SC);
   const int tiles_x = (g.nx + 2 * NG + AT_X - 1) / AT_X;
   const PlaneMap tpm = plane_map(tiles_x * ((g.nr + 2 * NG + AT_Y - 1) / AT_Y));
-  hipLaunchKernelGGL(k_adj_main, dim3(plane_map_grid(tpm, g)), dim3(256), 0, s, Q, M, g, ph, tpm,
-                     tiles_x, Rb, SC);
+  if (pt.x)
+    hipLaunchKernelGGL(k_adj_main<true>, dim3(plane_map_grid(tpm, g)), dim3(256), 0, s, Q, M, g, ph, pt,
+                       tpm, tiles_x, Rb, fr, SC);
+  else
+    hipLaunchKernelGGL(k_adj_main<false>, dim3(plane_map_grid(tpm, g)), dim3(256), 0, s, Q, M, g, ph,
+                       pt, tpm, tiles_x, Rb, fr, SC);
   const PlaneMap gpm = plane_map((g.plane + 255) / 256);
   hipLaunchKernelGGL(k_adj_gather, dim3(plane_map_grid(gpm, g)), dim3(256), 0, s, Q, g, ph, gpm, SC,
                      Qb);

@@ -772,8 +772,8 @@ int les_diagnostics_noalloc(les_ctx* c, const double* Qn, double* totals, double
   return LES_OK;
 }
 
-// Qb = (dR/dQ)^T Rb at Q (ghosts of Q filled here); inflow_bar accumulated.
-static int residual_vjp_into(les_ctx* c, double* Q, const double* Rb, double* Qb,
+// Qb = (dR/dQ)^T (fr Rb) at Q (ghosts of Q filled here); inflow_bar accumulated.
+static int residual_vjp_into(les_ctx* c, double* Q, const double* Rb, double fr, double* Qb,
                              double* inflow_bar, hipStream_t s) {
   int r = dalloc(c, (void**)&c->adj, (size_t)VJP_SCRATCH_VARS * c->g.vs * sizeof(double),
                  "adjoint scratch");
@@ -781,8 +781,8 @@ static int residual_vjp_into(les_ctx* c, double* Q, const double* Rb, double* Qb
   hipError_t e = ghosts<double>(c, Q, s);
   if (e == hipSuccess) {
     e = launch_residual_vjp(Q, (const double*)c->M, c->g, c->ph64, c->p.bc, c->p.ref_prim,
-                            c->p.p_exit, c->inflow, Rb, c->adj, Qb,
-                            c->p.bc[0] == LES_BC_INFLOW ? inflow_bar : nullptr, s);
+                            c->p.p_exit, c->inflow, Rb, fr, c->adj, Qb,
+                            c->p.bc[0] == LES_BC_INFLOW ? inflow_bar : nullptr, c->pt, s);
   }
   if (e != hipSuccess) return hip_fail(c, e, "residual adjoint kernels");
   return LES_OK;
@@ -813,7 +813,7 @@ int les_residual_vjp(les_ctx* c, double* Q, const double* Rbar, double* Qbar, do
   if (r != LES_OK) return r;
   if (!Q || !Rbar || !Qbar) return fail(c, LES_EINVAL, "Q, Rbar or Qbar is NULL");
   if (Q == Qbar || Q == Rbar) return fail(c, LES_EINVAL, "Q must not alias Rbar or Qbar");
-  return residual_vjp_into(c, Q, Rbar, Qbar, inflow_bar, (hipStream_t)stream);
+  return residual_vjp_into(c, Q, Rbar, 1.0, Qbar, inflow_bar, (hipStream_t)stream);
 }
 
 int les_rk5_step_vjp(les_ctx* c, double* Qn, double dt, const double* Qbar_np1, double* Qbar_n,
@@ -845,25 +845,28 @@ int les_rk5_step_vjp(les_ctx* c, double* Qn, double dt, const double* Qbar_np1, 
   }
   if (e != hipSuccess) return hip_fail(c, e, "rk5 adjoint forward kernels");
   // reverse: b5 = Qbar^(n+1); b(l-1) = -alpha_l dt J(Q^(l-1))^T b(l);
-  // Qbar^n = b5 + b4 + ... + b0
-  e = launch_scale(Qbar_np1, -al[4] * dt, B, v5, s);
-  if (e == hipSuccess) e = launch_interior_copy(Qbar_np1, Qbar_n, c->g, s);
-  // centerline through the nodes: the returned axis row is the mean of the
-  // returned row 1, so its cotangent goes to row 1 first
-  if (e == hipSuccess && c->p.bc[2] == LES_BC_AXIS_NODE) e = launch_centerline_transpose(B, c->g, s);
-  if (e == hipSuccess && c->p.bc[2] == LES_BC_AXIS_NODE)
-    e = launch_centerline_transpose(Qbar_n, c->g, s);
-  if (e != hipSuccess) return hip_fail(c, e, "rk5 adjoint kernels");
-  for (int l = 5; l >= 1; --l) {
-    if (l < 5) {
-      e = launch_scale(B, -al[l - 1] * dt, B, v5, s);
-      if (e != hipSuccess) return hip_fail(c, e, "rk5 adjoint kernels");
-    }
-    r = residual_vjp_into(c, X[l - 1], B, B, inflow_bar, s);
-    if (r != LES_OK) return r;
-    e = launch_accumulate(B, Qbar_n, v5, s);
+  // Qbar^n = b5 + b4 + ... + b0.  b4 goes to B; b(l-1), l < 5, to the buffer of
+  // Q^(l), which no later stage needs.
+  const double* b5 = Qbar_np1;
+  if (c->p.bc[2] == LES_BC_AXIS_NODE) {
+    // centerline through the nodes: the returned axis row is the mean of the
+    // returned row 1, so its cotangent goes to row 1 first
+    e = launch_interior_copy(Qbar_np1, Qbar_n, c->g, s);
+    if (e == hipSuccess) e = launch_centerline_transpose(Qbar_n, c->g, s);
     if (e != hipSuccess) return hip_fail(c, e, "rk5 adjoint kernels");
+    b5 = Qbar_n;
   }
+  const double* b[5];
+  const double* cot = b5;
+  for (int l = 5; l >= 1; --l) {
+    double* out = l == 5 ? B : X[l];
+    r = residual_vjp_into(c, X[l - 1], cot, -al[l - 1] * dt, out, inflow_bar, s);
+    if (r != LES_OK) return r;
+    b[5 - l] = out;
+    cot = out;
+  }
+  e = launch_step_sum(b5, b, Qbar_n, c->g, s);
+  if (e != hipSuccess) return hip_fail(c, e, "rk5 adjoint kernels");
   return LES_OK;
 }
 

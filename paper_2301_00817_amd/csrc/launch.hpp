@@ -97,7 +97,7 @@ hipError_t launch_diagnostics(const double* Q, const TM* M, const Grid& g, const
                               double* part, double* totals, double* s1, double* s2,
                               const ProdTab& pt, hipStream_t s);
 
-// Residual adjoint (FP64): Qb = (dR/dQ)^T Rb on the padded layout (ghost
+// Residual adjoint (FP64): Qb = (dR/dQ)^T (fr Rb) on the padded layout (ghost
 // entries zero); inflow_bar (5, nth, nr) accumulated when non-null.  Scratch
 // SC of VJP_SCRATCH_VARS padded variables; Q's ghosts must be filled.
 constexpr int VJP_SCRATCH_VARS = 28;
@@ -107,10 +107,12 @@ hipError_t launch_centerline_transpose(double* Qb, const Grid& g, hipStream_t s)
 
 hipError_t launch_residual_vjp(const double* Q, const double* M, const Grid& g,
                                const Phys<double>& ph, const int bc[6], const double ref_prim[5],
-                               double p_exit, const double* inflow, const double* Rb, double* SC,
-                               double* Qb, double* inflow_bar, hipStream_t s);
-hipError_t launch_scale(const double* x, double a, double* y, long long n, hipStream_t s);
+                               double p_exit, const double* inflow, const double* Rb, double fr,
+                               double* SC, double* Qb, double* inflow_bar, const ProdTab& pt,
+                               hipStream_t s);
 hipError_t launch_interior_copy(const double* x, double* y, const Grid& g, hipStream_t s);
-hipError_t launch_accumulate(const double* x, double* y, long long n, hipStream_t s);
+// y = x (interior) + b[0] + .. + b[4] in that order, 0 off the interior
+hipError_t launch_step_sum(const double* x, const double* const b[5], double* y, const Grid& g,
+                           hipStream_t s);
 
 }  // namespace lesjet

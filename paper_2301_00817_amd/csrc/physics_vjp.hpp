@@ -52,27 +52,33 @@ struct PointBar {
 
 // Given Gb[d][c] = dL/dG^d_c and lbb[d] = dL/dlambda_bar^d, accumulate into
 // `bar` (which the caller zeroes).  The sensors pass through the point
-// function unchanged; their cotangents are handled by sensor_vjp.
-template <typename T>
+// function unchanged; their cotangents are handled by sensor_vjp.  PROD: product
+// mesh: the terms of the zero metric terms are left out, and the tabulated
+// in.iV, in.len and in.d2 are used.
+template <bool PROD = false, typename T>
 __host__ __device__ inline void point_quantities_vjp(const PointIn<T>& in, const Phys<T>& ph,
                                                      const T Gb[3][5], const T lbb[3],
                                                      PointBar<T>& bar) {
   const T rho = in.q[0], u = in.pr[0], v = in.pr[1], w = in.pr[2], Tt = in.pr[3], p = in.pr[4];
   const T vel[3] = {u, v, w};
+  // S[d][m] is not identically zero
+  auto nz = [](int d, int m) { return !PROD || (d == 0) == (m == 0); };
   const T a = tsqrt(Tt);
   const T ia = trcp(a);                       // 1/T = ia^2
-  const T iV = trcp(in.V);
+  const T iV = PROD ? in.iV : trcp(in.V);
   const T aiV = tabs(iV);
   T Uc[3], Uc_b[3] = {0, 0, 0};
-  for (int d = 0; d < 3; ++d) Uc[d] = in.S[d][0] * u + in.S[d][1] * v + in.S[d][2] * w;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) Uc[d] = row_dot<PROD>(d, in.S[d], u, v, w);
   T a_b = 0, Tt_b = 0, p_b = 0, rho_b = 0;
   T vel_b[3] = {0, 0, 0};
 
   // spectral radii and their anisotropic scaling
   {
     T lam[3], Sn[3];
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
-      Sn[d] = tsqrt(in.S[d][0] * in.S[d][0] + in.S[d][1] * in.S[d][1] + in.S[d][2] * in.S[d][2]);
+      Sn[d] = PROD ? in.len[d] : row_norm<false>(d, in.S[d]);
       lam[d] = (tabs(Uc[d]) + a * Sn[d]) * aiV;
     }
     const T s01 = tsqrt(lam[0] * lam[1]);
@@ -94,9 +100,17 @@ __host__ __device__ inline void point_quantities_vjp(const PointIn<T>& in, const
   if (ph.viscous) {
     const T (&dl)[3][4] = in.dl;
     T g[4][3];
+#pragma unroll
     for (int f = 0; f < 4; ++f)
-      for (int m = 0; m < 3; ++m)
-        g[f][m] = (in.S[0][m] * dl[0][f] + in.S[1][m] * dl[1][f] + in.S[2][m] * dl[2][f]) * iV;
+#pragma unroll
+      for (int m = 0; m < 3; ++m) {
+        if (!PROD)
+          g[f][m] = (in.S[0][m] * dl[0][f] + in.S[1][m] * dl[1][f] + in.S[2][m] * dl[2][f]) * iV;
+        else if (m == 0)
+          g[f][m] = in.S[0][0] * dl[0][f] * iV;
+        else
+          g[f][m] = (in.S[1][m] * dl[1][f] + in.S[2][m] * dl[2][f]) * iV;
+      }
     const T iTS = trcp(Tt + ph.suth);
     const T mu = Tt * a * ph.suth1 * iTS;
     T mut = 0, Smag = 0, Csd2 = 0, sij[3][3];
@@ -106,8 +120,12 @@ __host__ __device__ inline void point_quantities_vjp(const PointIn<T>& in, const
     // sqrt(2 S_ij S_ij) (Smagorinsky) or sqrt(B_beta / alpha.alpha) / Delta^2
     // (Vreman)
     if (ph.sgs) {
-      const T delta = tcbrt(tabs(in.V));
-      Csd2 = ph.sgs_coef * delta * delta;
+      if (PROD) {
+        Csd2 = ph.sgs_coef * in.d2;
+      } else {
+        const T delta = tcbrt(tabs(in.V));
+        Csd2 = ph.sgs_coef * delta * delta;
+      }
       if (ph.sgs == 1) {
         T s2 = 0;
         for (int i = 0; i < 3; ++i)
@@ -127,8 +145,11 @@ __host__ __device__ inline void point_quantities_vjp(const PointIn<T>& in, const
     const T kap = (mu * ph.Pr_inv + mut * ph.Prs_inv) * ph.igm1;
     // G[d][1+i] -= Cv S[d].tau[i];  G[d][4] -= Cv S[d].beta
     T tau_b[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, beta_b[3] = {0, 0, 0};
+#pragma unroll
     for (int d = 0; d < 3; ++d)
+#pragma unroll
       for (int j = 0; j < 3; ++j) {
+        if (!nz(d, j)) continue;
         for (int i = 0; i < 3; ++i) tau_b[i][j] -= ph.Cv * Gb[d][1 + i] * in.S[d][j];
         beta_b[j] -= ph.Cv * Gb[d][4] * in.S[d][j];
       }
@@ -172,29 +193,38 @@ __host__ __device__ inline void point_quantities_vjp(const PointIn<T>& in, const
     // Sutherland: dmu/dT = mu (3/(2T) - 1/(T + S))
     Tt_b += mu_b * mu * (T(1.5) * ia * ia - iTS);
     // g[f][m] = iV sum_d S[d][m] dl[d][f]
+#pragma unroll
     for (int d = 0; d < 3; ++d)
+#pragma unroll
       for (int f = 0; f < 4; ++f) {
         T acc = 0;
-        for (int m = 0; m < 3; ++m) acc += in.S[d][m] * g_b[f][m];
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+          if (nz(d, m)) acc += in.S[d][m] * g_b[f][m];
         bar.dl[d][f] += acc * iV;
       }
   }
 
   // inviscid point fluxes
+#pragma unroll
   for (int d = 0; d < 3; ++d) {
     rho_b += Gb[d][0] * Uc[d];
     Uc_b[d] += Gb[d][0] * rho;
+#pragma unroll
     for (int i = 0; i < 3; ++i) {
       Uc_b[d] += Gb[d][1 + i] * in.q[1 + i];
       bar.q[1 + i] += Gb[d][1 + i] * Uc[d];
-      p_b += Gb[d][1 + i] * in.S[d][i];
+      if (nz(d, i)) p_b += Gb[d][1 + i] * in.S[d][i];
     }
     Uc_b[d] += Gb[d][4] * (in.q[4] + p);
     bar.q[4] += Gb[d][4] * Uc[d];
     p_b += Gb[d][4] * Uc[d];
   }
+#pragma unroll
   for (int d = 0; d < 3; ++d)
-    for (int i = 0; i < 3; ++i) vel_b[i] += Uc_b[d] * in.S[d][i];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (nz(d, i)) vel_b[i] += Uc_b[d] * in.S[d][i];
   Tt_b += T(0.5) * a_b * ia;
   bar.q[0] += rho_b;
   bar.pr[0] += vel_b[0];
