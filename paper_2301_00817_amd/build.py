@@ -21,7 +21,7 @@ LIB = os.path.join(LIBDIR, "liblesjet.so")
 ARCH = os.environ.get("LESJET_ARCH", "gfx950")
 
 SOURCES = ["api.cpp", "geometry.hip", "ghost.hip", "residual_ref.hip", "residual_fused.hip",
-           "residual_fused32.hip", "rk.hip", "diag.hip", "adjoint.hip", "dynamic.hip"]
+           "residual_fused_wide.hip", "residual_fused32.hip", "rk.hip", "diag.hip", "adjoint.hip", "dynamic.hip"]
 
 CFLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -37,7 +37,8 @@ CFLAGS = [
 # default scheduling.  The FP32 stage kernel (residual_fused32.hip) keeps the
 # default, under which it fits four waves per SIMD without spilling (3 %
 # faster than with the ILP scheduling, which spills).
-SOURCE_FLAGS = {"residual_fused.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+_MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
+SOURCE_FLAGS = {"residual_fused.hip": _MAX_ILP, "residual_fused_wide.hip": _MAX_ILP}
 
 # Host-side ranges around the API calls and RK stages for rocprofv3
 # --marker-trace (ROCTx; inert when no tool is attached).

@@ -54,7 +54,7 @@ struct les_ctx {
   Phys<float> ph32;
   int device = 0;
   int num_cu = 256;
-  int kc = 16;                 // k-chunk of the fused kernel
+  FusedPlan plan = {16, false};   // tile and k-chunk of the stage kernel
   double* coords = nullptr;    // padded coordinates (3 ghost layers), freed by les_metrics
   double* prod = nullptr;      // tables of a product mesh (NULL otherwise)
   ProdTab pt;                  // and their parts
@@ -397,11 +397,11 @@ int les_init_grid(les_ctx** out, const les_params* p, const double* xyz, const d
   if (e != hipSuccess) { delete c; return hip_fail(nullptr, e, "hipGetSymbolAddress(scratch)"); }
   e = hipDeviceGetAttribute(&c->num_cu, hipDeviceAttributeMultiprocessorCount, c->device);
   if (e != hipSuccess) { delete c; return hip_fail(nullptr, e, "hipDeviceGetAttribute"); }
-  c->kc = p->precision == LES_FP32_STORAGE ? fused_chunk<float>(c->g, c->num_cu)
-                                          : fused_chunk<double>(c->g, c->num_cu);
+  c->plan = p->precision == LES_FP32_STORAGE ? fused_plan<float>(c->g, c->num_cu)
+                                            : fused_plan<double>(c->g, c->num_cu);
   if (const char* kc = std::getenv("LESJET_KCHUNK")) {   // tuning / test override
     const int v = std::atoi(kc);
-    if (v >= 1) c->kc = v;
+    if (v >= 1) c->plan.kc = v;
   }
   hipStream_t s = (hipStream_t)stream;
   r = dalloc(c, (void**)&c->coords, (size_t)3 * c->cg.vs * sizeof(double), "coordinates");
@@ -543,7 +543,7 @@ static int residual_into(les_ctx* c, T* Q, T* R_out, hipStream_t s) {
   if (e == hipSuccess && dynamic_model(c)) e = dynamic_coefs<T>(c, Q, s);
   if (e == hipSuccess) {
     const long k = prof_begin(c, s);
-    e = launch_fused<T>(Q, (const T*)c->M, c->g, phys<T>(c), c->kc, FUSED_EPI_R, R_out, nullptr,
+    e = launch_fused<T>(Q, (const T*)c->M, c->g, phys<T>(c), c->plan, FUSED_EPI_R, R_out, nullptr,
                         nullptr, 0.0, nullptr, c->ph64, nullptr, FUSED_LAG_NONE, nullptr, c->dyn,
                         c->pt, s);
     prof_end(c, k, s);
@@ -695,7 +695,7 @@ static int rk5_steps(les_ctx* c, double* Qn, int nsteps, double dt_fixed, double
       }
       const int lag = !lagv ? FUSED_LAG_NONE : (l == 0 ? FUSED_LAG_WRITE : FUSED_LAG_READ);
       const long k = prof_begin(c, s);
-      e = launch_fused<T>(src, M, c->g, phys<T>(c), c->kc, epi, dst, Qn, q64, c->p.rk_alpha[l],
+      e = launch_fused<T>(src, M, c->g, phys<T>(c), c->plan, epi, dst, Qn, q64, c->p.rk_alpha[l],
                           c->dt, c->ph64, c->maxbits, lag, (T*)c->visc, c->dyn, c->pt, s);
       prof_end(c, k, s);
       src = dst;
@@ -839,7 +839,7 @@ int les_rk5_step_vjp(les_ctx* c, double* Qn, double dt, const double* Qbar_np1, 
   for (int l = 1; l <= 4 && e == hipSuccess; ++l) {
     e = ghosts<double>(c, X[l - 1], s);
     if (e == hipSuccess)
-      e = launch_fused<double>(X[l - 1], (const double*)c->M, c->g, c->ph64, c->kc, FUSED_EPI_RK,
+      e = launch_fused<double>(X[l - 1], (const double*)c->M, c->g, c->ph64, c->plan, FUSED_EPI_RK,
                                X[l], Qn, nullptr, al[l - 1], c->dt, c->ph64, c->maxbits,
                                FUSED_LAG_NONE, nullptr, nullptr, c->pt, s);
   }

@@ -1,7 +1,7 @@
 // Fused residual / Runge-Kutta stage kernel (section "Spatial
 // Discretization" with the stage update of eq. localdt as an epilogue).
 //
-// Work decomposition (2.5-D): a block of Tile<T>::X x Tile<T>::Y threads
+// Work decomposition (2.5-D): a block of Tile::X x Tile::Y threads
 // owns a ring-1 tile of (i, j) columns and marches along k over a chunk of
 // planes.  For each plane kk it
 //   (a) writes the state and primitives of the plane (ring-2 tile, two-point
@@ -17,7 +17,8 @@
 //       previous iteration), which completes R at plane kk-1.
 // Every point quantity of a ring-1 column is computed once per plane, every
 // face flux once.  HBM traffic per interior point and stage: Q (in), the 10
-// metric arrays, Q^(0) and the output, the halos coming from L2.
+// metric arrays (none on a product mesh), Q^(0) and the output, the halos
+// coming from L2.
 //
 // Epilogues: EPI_R writes R; EPI_RK writes Q^(l) = Q^(0) - alpha dt R
 // (accumulated in FP64, stored in the stage type); EPI_RK_LAST also writes
@@ -31,13 +32,17 @@
 
 namespace lesjet {
 
-// Tile shape per precision (threads along i and j of a ring-1 tile):
-// FP64 16 x 16 (LDS 79 KB, two blocks per CU), FP32 32 x 8 (LDS 40 KB, four
-// blocks per CU); both measured fastest among 64x8, 32x8 and 16x16 on the
-// jet meshes.
-template <typename T> struct Tile;
-template <> struct Tile<double> { static constexpr int X = 16, Y = 16, PER_CU = 2; };
-template <> struct Tile<float> { static constexpr int X = 32, Y = 8, PER_CU = 4; };
+// Tile shapes (threads along i and j of a ring-1 tile): FP64 16 x 16 (LDS 57
+// KB, two blocks per CU) or, WIDE, 32 x 16 (LDS 107 KB, one block of eight
+// waves), FP32 32 x 8 (LDS 29 KB, four blocks per CU).  The wide tile computes
+// 512 ring-1 columns for 420 outputs, the narrow one 256 for 196 (7 % more):
+// 21.6 against 23.5 ms a step on 102 M points, 440 against 501 us a residual
+// of a 200^3 curvilinear mesh (before the xi faces left LDS the two were
+// within 1 %).  fused_plan picks the tile that a mesh's extents waste less of.
+template <typename T, bool WIDE> struct Tile;
+template <> struct Tile<double, false> { static constexpr int X = 16, Y = 16, PER_CU = 2; };
+template <> struct Tile<double, true> { static constexpr int X = 32, Y = 16, PER_CU = 1; };
+template <> struct Tile<float, false> { static constexpr int X = 32, Y = 8, PER_CU = 4; };
 
 constexpr int NPQ = 8;                // G(5), lambda_bar, nu, V per direction
 
@@ -121,8 +126,8 @@ template <> struct FusedOccE<float, EPI_RK_LAST, false> { static constexpr int w
 // hardware reciprocal, root and logarithm cost no more than the products)
 // spare a reciprocal, two roots and a cube root of the 850 vector operations
 // per point and plane: another 3 % (24.0 -> 23.1 ms on 102 M points).
-template <typename T, int EPI, bool AXIS, int LAG, bool DYN, bool PROD>
-__global__ void __launch_bounds__(Tile<T>::X * Tile<T>::Y, (FusedOccE<T, EPI, PROD>::waves))
+template <typename T, bool WIDE, int EPI, bool AXIS, int LAG, bool DYN, bool PROD>
+__global__ void __launch_bounds__((Tile<T, WIDE>::X * Tile<T, WIDE>::Y), (FusedOccE<T, EPI, PROD>::waves))
 k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_arg, int kc,
         TileMap tm, T* out, const double* Q0, double* Q64, double alpha,
         const double* __restrict__ dtp, Phys<double> ph64, unsigned long long* __restrict__ maxbits,
@@ -133,8 +138,8 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     ph.Prs_inv = (T)dyn[1];
     ph.iso_coef = (T)dyn[2];
   }
-  constexpr int FB_X = Tile<T>::X;              // threads along i (ring-1 columns)
-  constexpr int FB_Y = Tile<T>::Y;              // threads along j
+  constexpr int FB_X = Tile<T, WIDE>::X;        // threads along i (ring-1 columns)
+  constexpr int FB_Y = Tile<T, WIDE>::Y;        // threads along j
   constexpr int FT_X = FB_X - 2;                // interior outputs along i
   constexpr int FT_Y = FB_Y - 2;                // interior outputs along j
   constexpr int FR_X = FB_X + 2;                // ring-2 tile
@@ -535,49 +540,53 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   }
 }
 
-template <typename T>
-int fused_chunk(const Grid& g, int num_cu) {
-  constexpr int FT_X = Tile<T>::X - 2, FT_Y = Tile<T>::Y - 2;
-  num_cu *= Tile<T>::PER_CU;          // resident blocks (the FP32 last stage, at
-                                      // three per CU, takes the same length)
-  const long long tiles = (long long)((g.nx + FT_X - 1) / FT_X) * ((g.nr + FT_Y - 1) / FT_Y);
-  // pick the chunk length that minimises (rounds of resident blocks) x (planes per block),
-  // over every length up to the cap (a mesh that fits one round takes the
-  // shortest chunks that still do: 32^3, single planes, three iterations per
-  // block, 15.8 us a residual against 20.1 us with four; FP32 keeps at least
-  // four, as its states depend on the chunk length by up to 6e-8, the rounding of
-  // a chunk's first planes in its prologue; lengths that divide the azimuth
-  // leave no short last chunk: against powers of two only, 5.6 % on the 128 x
-  // 128 x 360 mesh and 3.1 % on 1700 x 1700 x 360 in FP64, 1.4-1.6 % in FP32,
-  // 0.5 % on 1250 x 640 x 1250).
-  // FP32 (four blocks per CU) stops at 16 planes: longer chunks measured
-  // slower on large meshes (4 % at 1e8 points, 8 % at 1e9), the resident
-  // blocks of a round drifting apart in k and sharing fewer halo lines in
-  // L2.  FP64 (two blocks per CU) takes 64 planes when that fits one round
-  // (the 5.9 M-point mesh: 4 % faster than 32) and at most 32 otherwise:
-  // the same time within 1 % on 1e8 and 1e9 points, with 12 % (32) to 21 %
-  // (16) fewer bytes crossing the L2 boundary than with 64.
-  const auto choose = [&](int kc_max, long long* rounds_out) {
-    int best = g.nth;
-    long long best_rounds = 0;
-    double best_cost = 1e300;
+// Chunk length that minimises (rounds of resident blocks) x (planes per block),
+// over every length up to the cap (a mesh that fits one round takes the
+// shortest chunks that still do: 32^3, single planes, three iterations per
+// block, 15.8 us a residual on the narrow tile against 20.1 us with four; FP32 keeps at least
+// four, as its states depend on the chunk length by up to 6e-8, the rounding of
+// a chunk's first planes in its prologue; lengths that divide the azimuth
+// leave no short last chunk: against powers of two only, 5.6 % on the 128 x
+// 128 x 360 mesh and 3.1 % on 1700 x 1700 x 360 in FP64, 1.4-1.6 % in FP32,
+// 0.5 % on 1250 x 640 x 1250).
+// FP32 (four blocks per CU; the last stage, at three on general meshes, takes
+// the same length) stops at 16 planes: longer chunks measured slower on large
+// meshes (4 % at 1e8 points, 8 % at 1e9), the resident blocks of a round
+// drifting apart in k and sharing fewer halo lines in L2.  FP64 takes 64 planes
+// when that fits one round (the 5.9 M-point mesh: 4 % faster than 32) and at
+// most 32 otherwise: the same time within 1 % on 1e8 and 1e9 points, with 12 %
+// (32) to 21 % (16) fewer bytes crossing the L2 boundary than with 64.
+template <typename T, bool WIDE>
+FusedPlan tile_plan(const Grid& g, int num_cu, double* cost_out) {
+  using TL = Tile<T, WIDE>;
+  const long long tiles = (long long)((g.nx + TL::X - 3) / (TL::X - 2)) *
+                          ((g.nr + TL::Y - 3) / (TL::Y - 2));
+  const long long resident = (long long)num_cu * TL::PER_CU;
+  FusedPlan best = {g.nth, WIDE};
+  long long best_blocks = 0;
+  const auto choose = [&](int kc_max) {
+    *cost_out = 1e300;
     for (int kc = sizeof(T) == 8 ? 1 : 4; kc <= kc_max; ++kc) {
       const long long nb = tiles * ((g.nth + kc - 1) / kc);
-      const long long rounds = (nb + num_cu - 1) / num_cu;
-      const double cost = (double)rounds * (kc + 2);
-      if (cost < best_cost) { best_cost = cost; best = kc; best_rounds = rounds; }
+      const double cost = (double)((nb + resident - 1) / resident) * (kc + 2);
+      if (cost < *cost_out) { *cost_out = cost; best.kc = kc; best_blocks = nb; }
     }
-    *rounds_out = best_rounds;
-    return best;
   };
-  long long rounds = 0;
-  if (sizeof(T) == 4) return choose(16, &rounds);
-  const int kc64 = choose(64, &rounds);
-  return rounds <= 1 ? kc64 : choose(32, &rounds);
+  if (sizeof(T) == 4) {
+    choose(16);
+    return best;
+  }
+  choose(64);
+  if (best_blocks > resident) choose(32);
+  // four waves alone on a CU take a plane in about 0.8 of the time of eight
+  // (16^3, every block alone on its CU: 13.4 against 14.8 us, 7 us of them the
+  // launches)
+  if (!WIDE && best_blocks <= num_cu) *cost_out *= 0.8;
+  return best;
 }
 
-template <typename T>
-hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph, int kc, int epi,
+template <typename T, bool WIDE>
+hipError_t launch_fused_tile(const T* Q, const T* M, const Grid& g, const Phys<T>& ph, int kc, int epi,
                         T* out, const double* Q0, double* Q64, double alpha, const double* dt,
                         const Phys<double>& ph64, unsigned long long* maxbits, int lag, T* visc,
                         const double* dyn, const ProdTab& pt, hipStream_t s) {
@@ -586,13 +595,14 @@ hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph
   // LAG_READ with EPI_RK and EPI_RK_LAST (stages 2-5)
   if (lag != LAG_NONE && (!visc || epi == EPI_R || (lag == LAG_WRITE && epi != EPI_RK)))
     return hipErrorInvalidValue;
-  constexpr int FT_X = Tile<T>::X - 2, FT_Y = Tile<T>::Y - 2;
+  using TL = Tile<T, WIDE>;
+  constexpr int FT_X = TL::X - 2, FT_Y = TL::Y - 2;
   const TileMap tm = tile_map((g.nx + FT_X - 1) / FT_X, (g.nr + FT_Y - 1) / FT_Y,
                               (g.nth + kc - 1) / kc);
   const dim3 grid((unsigned)(tm.per_xcd * NXCD));
-  const dim3 block(Tile<T>::X, Tile<T>::Y, 1);
+  const dim3 block(TL::X, TL::Y, 1);
 #define LESJET_FUSED_P(E, A, L, D, P)                                                  \
-  hipLaunchKernelGGL((k_fused<T, E, A, L, D, P>), grid, block, 0, s, Q, M, g, ph, kc, tm, \
+  hipLaunchKernelGGL((k_fused<T, WIDE, E, A, L, D, P>), grid, block, 0, s, Q, M, g, ph, kc, tm, \
                      out, Q0, Q64, alpha, dt, ph64, maxbits, visc, dyn, pt)
 #define LESJET_FUSED(E, A, L)                                                          \
   do {                                                                                 \

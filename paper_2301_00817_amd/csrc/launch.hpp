@@ -43,13 +43,18 @@ template <typename T>
 hipError_t launch_residual_ref(const T* Q, const T* M, const Grid& g, const Phys<T>& ph, T* PT,
                                T* R, hipStream_t s);
 
+// Tile (see fused_stage.hpp) and planes per block of the stage kernel.
+struct FusedPlan {
+  int kc;
+  bool wide;
+};
 template <typename T>
-int fused_chunk(const Grid& g, int num_cu);
+FusedPlan fused_plan(const Grid& g, int num_cu);
 
 // dyn: coefficients of the dynamic SGS model (device, see launch_dynamic),
 // read when ph.sgs == 3; may be NULL otherwise.
 template <typename T>
-hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph, int kc, int epi,
+hipError_t launch_fused(const T* Q, const T* M, const Grid& g, const Phys<T>& ph, FusedPlan plan, int epi,
                         T* out, const double* Q0, double* Q64, double alpha, const double* dt,
                         const Phys<double>& ph64, unsigned long long* maxbits, int lag, T* visc,
                         const double* dyn, const ProdTab& pt, hipStream_t s);

@@ -7,11 +7,19 @@
 
 namespace lesjet {
 
-template int fused_chunk<float>(const Grid&, int);
-template hipError_t launch_fused<float>(const float*, const float*, const Grid&, const Phys<float>&,
-                                        int, int, float*, const double*, double*, double,
-                                        const double*, const Phys<double>&, unsigned long long*,
-                                        int, float*, const double*,
-                                         const ProdTab&, hipStream_t);
+template <>
+FusedPlan fused_plan<float>(const Grid& g, int num_cu) {
+  double cost;
+  return tile_plan<float, false>(g, num_cu, &cost);
+}
+
+template <>
+hipError_t launch_fused<float>(const float* Q, const float* M, const Grid& g, const Phys<float>& ph,
+                        FusedPlan plan, int epi, float* out, const double* Q0, double* Q64, double alpha, const double* dt,
+                        const Phys<double>& ph64, unsigned long long* maxbits, int lag, float* visc,
+                        const double* dyn, const ProdTab& pt, hipStream_t s) {
+  return launch_fused_tile<float, false>(
+      Q, M, g, ph, plan.kc, epi, out, Q0, Q64, alpha, dt, ph64, maxbits, lag, visc, dyn, pt, s);
+}
 
 }  // namespace lesjet
