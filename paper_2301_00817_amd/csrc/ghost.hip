@@ -91,15 +91,19 @@ __device__ __forceinline__ void xi_value(const T* __restrict__ Q, const Grid& g,
 // eta layers (i padded, k interior), the xi layers (j, k interior).
 // held != nullptr: a ghost point whose trace ends in a physical-face rule
 // (entrance, exit, far field) takes the value of `held` at the same point,
-// which is that rule evaluated on the held state.
-// 64-thread blocks, at least six waves per SIMD: the FP64 instance fits 80
-// VGPRs without spilling (81 unbounded, five waves); eight waves spill.
+// which is that rule evaluated on the held state, and so does the axis row of a
+// centerline through the nodes: held_axis, further threads copy it, and ghost
+// points that trace to it read `held` (a launch of its own for the row took
+// 5 us and a gap of 8 us a stage of the 0.4 M-point jet).
+// 64-thread blocks, at least five waves per SIMD: the FP64 instance takes 81
+// VGPRs; asked for six waves it spills two (the same times within 0.5 %), for
+// eight many.
 constexpr int GH_BS = 64;
 template <typename T>
-__global__ __launch_bounds__(GH_BS, 6) void k_ghost_all(T* __restrict__ Q, Grid g, const T* __restrict__ M,
+__global__ __launch_bounds__(GH_BS, 5) void k_ghost_all(T* __restrict__ Q, Grid g, const T* __restrict__ M,
                             const double* __restrict__ inflow, double gamma, int xlo, int xhi,
                             int elo, int ehi, double p_exit, BPrim<T> ref,
-                            const T* __restrict__ held) {
+                            const T* __restrict__ held, int held_axis) {
   // 32-bit index arithmetic: the ghost points number 4 (NX NR + NX nth +
   // nr nth), far below 2^32 for every mesh the library accepts
   const unsigned NX = g.nx + 2 * NG, NR = g.nr + 2 * NG, nth = g.nth, nr = g.nr;
@@ -124,11 +128,16 @@ __global__ __launch_bounds__(GH_BS, 6) void k_ghost_all(T* __restrict__ Q, Grid 
     const unsigned r = t / (2 * NG);
     j = (int)(r % nr);
     k = (int)(r / nr);
+  } else if (held_axis && (t -= nxg) < (unsigned)g.nx * nth) {
+    k = (int)(t / (unsigned)g.nx);
+    i = (int)(t - (unsigned)k * (unsigned)g.nx);
+    j = 0;
   } else {
     return;
   }
   const int og = g.at(i, j, k);
-  if (held && ((i < 0 && xlo != BC_PERIODIC) || (i >= g.nx && xhi != BC_PERIODIC) ||
+  const bool axis_row = held_axis && j == 0 && i >= 0 && i < g.nx;
+  if (held && (axis_row || (i < 0 && xlo != BC_PERIODIC) || (i >= g.nx && xhi != BC_PERIODIC) ||
                (j >= g.nr && ehi != BC_PERIODIC))) {
     T h[5];
     load5(held, g.vs, og, h);
@@ -137,11 +146,12 @@ __global__ __launch_bounds__(GH_BS, 6) void k_ghost_all(T* __restrict__ Q, Grid 
   }
   // zeta sweep (periodic): the wrapped point
   int kw = k < 0 ? k + g.nth : (k >= g.nth ? k - g.nth : k);
+  const T* src = held_axis && j == 0 ? held : Q;
   const int an = elo == BC_AXIS_NODE;
   // eta sweep
   T q[5];
   if (j >= 0 && j < g.nr) {
-    xi_value(Q, g, M, inflow, gamma, xlo, xhi, p_exit, an, i, j, kw, q);
+    xi_value(src, g, M, inflow, gamma, xlo, xhi, p_exit, an, i, j, kw, q);
   } else if (j < 0) {
     if (elo == BC_PERIODIC)
       xi_value(Q, g, M, inflow, gamma, xlo, xhi, p_exit, an, i, j + g.nr, kw, q);
@@ -167,16 +177,6 @@ __global__ __launch_bounds__(GH_BS, 6) void k_ghost_all(T* __restrict__ Q, Grid 
 // of the conserved variables of row j = 1 (one block per i, a fixed-order
 // FP64 tree over k, so the value is the same for every k and reproducible).
 constexpr int CL_BS = 256;
-
-// held row (schedule with held boundary values)
-template <typename T>
-__global__ void k_centerline_held(T* __restrict__ Q, Grid g, const T* __restrict__ held) {
-  const int i = blockIdx.x;
-  for (int k = threadIdx.x; k < g.nth; k += blockDim.x) {
-    const int o = g.at(i, 0, k);
-    for (int c = 0; c < 5; ++c) Q[(long long)c * g.vs + o] = held[(long long)c * g.vs + o];
-  }
-}
 
 template <typename T>
 __global__ void k_centerline(T* __restrict__ Q, Grid g) {
@@ -210,20 +210,18 @@ template <typename T>
 hipError_t launch_ghosts(T* Q, const Grid& g, const T* M, const double* inflow,
                          const Phys<T>& ph, const int bc[6], const double ref_prim[5],
                          double p_exit, const T* held, hipStream_t s) {
-  if (bc[2] == BC_AXIS_NODE) {
-    if (held)
-      hipLaunchKernelGGL(k_centerline_held<T>, dim3(g.nx), dim3(CL_BS), 0, s, Q, g, held);
-    else
-      hipLaunchKernelGGL(k_centerline<T>, dim3(g.nx), dim3(CL_BS), 0, s, Q, g);
-  }
+  const bool axis = bc[2] == BC_AXIS_NODE, held_axis = axis && held;
+  if (axis && !held)
+    hipLaunchKernelGGL(k_centerline<T>, dim3(g.nx), dim3(CL_BS), 0, s, Q, g);
   const double gamma = (double)ph.gamma;
   BPrim<T> ref;
   ref.rho = (T)ref_prim[0]; ref.u = (T)ref_prim[1]; ref.v = (T)ref_prim[2];
   ref.w = (T)ref_prim[3]; ref.p = (T)ref_prim[4];
   const long long NX = g.nx + 2 * NG, NR = g.nr + 2 * NG;
-  const long long n = 2LL * NG * (NX * NR + NX * g.nth + (long long)g.nr * g.nth);
+  const long long n = 2LL * NG * (NX * NR + NX * g.nth + (long long)g.nr * g.nth) +
+                      (held_axis ? (long long)g.nx * g.nth : 0);
   hipLaunchKernelGGL(k_ghost_all<T>, dim3(blocks_for(n, GH_BS)), dim3(GH_BS), 0, s, Q, g, M, inflow,
-                     gamma, bc[0], bc[1], bc[2], bc[3], p_exit, ref, held);
+                     gamma, bc[0], bc[1], bc[2], bc[3], p_exit, ref, held, (int)held_axis);
   return hipGetLastError();
 }
 
