@@ -22,7 +22,8 @@ The JSON line also carries
                the new stage state): FP64 280 B, FP32 storage 168 B averaged
                over the five stages.  `fused` gives the same kernel against
                the bytes it moves itself (R never leaves the chip: 200 B,
-               FP32 storage 128 B).  `traffic` is the HBM bytes per launch
+               FP32 storage 128 B; 80 B and 40 B less on a product mesh, whose
+               metric terms are not read).  `traffic` is the HBM bytes per launch
                measured by rocprofv3 FETCH_SIZE + WRITE_SIZE
                (profiles/traffic.json) when those counters were taken on the
                current kernel sources and on this workload, else null;
@@ -72,6 +73,8 @@ METHOD_STAGE_BYTES = {"fp64": 280.0, "fp32": 168.0}
 # state (5) and the metrics (10), read Q^(0) (5 FP64), write the stage state
 # (5).  FP64: 200 B.  FP32 storage: 20 + 40 + 40 + 20 = 120 B, plus 40 B for
 # the FP64 Q^(n+1) in the last stage, i.e. 128 B averaged over the stages.
+# A product mesh (every jet here) forms the metric terms from tables and moves
+# 80 B (FP32 storage 40 B) less; the figures stay those of a general mesh.
 FUSED_STAGE_BYTES = {"fp64": (5 + 10 + 5 + 5) * 8.0, "fp32": (5 + 10 + 5) * 4 + 5 * 8 + 5 * 8 / 5}
 # The per-step update schedule (viscosities held from stage 1) adds two
 # values per point: written by the first stage, read by the four others.
