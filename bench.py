@@ -85,7 +85,8 @@ DOMINANT_KERNEL = "k_fused"
 # the sources the stage kernel is compiled from and its compiler flags (its
 # traffic record is tied to them)
 STAGE_SOURCES = ("common.hpp", "physics.hpp", "plane_io.hpp", "tiles.hpp", "fused_stage.hpp",
-                 "residual_fused.hip", "residual_fused_wide.hip", "residual_fused32.hip")
+                 "residual_fused.hip", "residual_fused_wide.hip", "residual_fused32.hip",
+                 "residual_fused32_wide.hip")
 
 
 def source_hash():

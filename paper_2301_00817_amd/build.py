@@ -21,7 +21,8 @@ LIB = os.path.join(LIBDIR, "liblesjet.so")
 ARCH = os.environ.get("LESJET_ARCH", "gfx950")
 
 SOURCES = ["api.cpp", "geometry.hip", "ghost.hip", "residual_ref.hip", "residual_fused.hip",
-           "residual_fused_wide.hip", "residual_fused32.hip", "rk.hip", "diag.hip", "adjoint.hip", "dynamic.hip"]
+           "residual_fused_wide.hip", "residual_fused32.hip",
+           "residual_fused32_wide.hip", "rk.hip", "diag.hip", "adjoint.hip", "dynamic.hip"]
 
 CFLAGS = [
     "-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -34,7 +35,7 @@ CFLAGS = [
 
 # Per-source flags.  The FP64 stage kernel (bound by latency) is scheduled for
 # instruction-level parallelism: 0.7 % less time per launch on MI355X than the
-# default scheduling.  The FP32 stage kernel (residual_fused32.hip) keeps the
+# default scheduling.  The FP32 stage kernel (residual_fused32*.hip) keeps the
 # default, under which it fits four waves per SIMD without spilling (3 %
 # faster than with the ILP scheduling, which spills).
 _MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]

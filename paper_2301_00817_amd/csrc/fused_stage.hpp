@@ -34,7 +34,8 @@ namespace lesjet {
 
 // Tile shapes (threads along i and j of a ring-1 tile): FP64 16 x 16 (LDS 57
 // KB, two blocks per CU) or, WIDE, 32 x 16 (LDS 107 KB, one block of eight
-// waves), FP32 32 x 8 (LDS 29 KB, four blocks per CU).  The wide tile computes
+// waves), FP32 32 x 8 (LDS 29 KB, four blocks per CU) or, WIDE, 32 x 16 (55
+// KB, two blocks).  In FP64 the wide tile computes
 // 512 ring-1 columns for 420 outputs, the narrow one 256 for 196 (7 % more):
 // 21.6 against 23.5 ms a step on 102 M points, 440 against 501 us a residual
 // of a 200^3 curvilinear mesh (before the xi faces left LDS the two were
@@ -43,6 +44,7 @@ template <typename T, bool WIDE> struct Tile;
 template <> struct Tile<double, false> { static constexpr int X = 16, Y = 16, PER_CU = 2; };
 template <> struct Tile<double, true> { static constexpr int X = 32, Y = 16, PER_CU = 1; };
 template <> struct Tile<float, false> { static constexpr int X = 32, Y = 8, PER_CU = 4; };
+template <> struct Tile<float, true> { static constexpr int X = 32, Y = 16, PER_CU = 2; };
 
 constexpr int NPQ = 8;                // G(5), lambda_bar, nu, V per direction
 
@@ -552,7 +554,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
 // leave no short last chunk: against powers of two only, 5.6 % on the 128 x
 // 128 x 360 mesh and 3.1 % on 1700 x 1700 x 360 in FP64, 1.4-1.6 % in FP32,
 // 0.5 % on 1250 x 640 x 1250).
-// FP32 (four blocks per CU; the last stage, at three on general meshes, takes
+// FP32 (four waves per SIMD; the last stage, at three on general meshes, takes
 // the same length) stops at 16 planes: longer chunks measured slower on large
 // meshes (4 % at 1e8 points, 8 % at 1e9), the resident blocks of a round
 // drifting apart in k and sharing fewer halo lines in L2.  FP64 takes 64 planes
