@@ -168,7 +168,9 @@ int les_validate(const les_params* p);
  * 2^31 - 1 elements. */
 int les_layout(const les_params* p, int64_t* pitch, int64_t dims[3], int64_t* var_stride);
 
-/* Device bytes the context will hold (metrics + stage buffers + scratch). */
+/* Device bytes the context will hold for time steps (metrics, entrance data, stage
+ * buffers, dynamic-model fields and the metric tables of a product mesh, 64 bytes
+ * per padded (j, k) and 32 per padded i, which any other mesh does not keep). */
 int les_device_bytes(const les_params* p, size_t* bytes);
 
 /* ---- context ------------------------------------------------------------ */

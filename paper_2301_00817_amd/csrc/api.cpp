@@ -327,7 +327,8 @@ int les_device_bytes(const les_params* p, size_t* bytes) {
   const size_t ts = storage_size(p);
   // metrics + two stage states (the two-pass reference form adds 21 scratch
   // variables when it is used); the per-step schedule adds the two held
-  // viscosities and, in FP32, a third stage state
+  // viscosities and, in FP32, a third stage state; the tables of a product mesh
+  // (a general mesh gives them back in les_metrics)
   size_t vars = 10 + 5 + 5;
   if (p->sgs_model == LES_SGS_DYNAMIC && p->visc_coef != 0.0)
     vars += (size_t)DYN_SCRATCH_VARS * sizeof(double) / ts;
@@ -335,7 +336,8 @@ int les_device_bytes(const les_params* p, size_t* bytes) {
     if (p->visc_coef != 0.0) vars += 2;
     if (p->precision == LES_FP32_STORAGE) vars += 5;
   }
-  *bytes = (size_t)g.vs * ts * vars + (size_t)5 * p->nth * p->nr * sizeof(double);
+  *bytes = (size_t)g.vs * ts * vars +
+           ((size_t)5 * p->nth * p->nr + prod_tab_doubles(g)) * sizeof(double);
   return LES_OK;
 }
 

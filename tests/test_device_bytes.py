@@ -1,0 +1,46 @@
+"""les_device_bytes: what a context holds for time steps, the metric tables of a
+product mesh (eight doubles per padded (j, k), four per padded i) among it.  Thin
+meshes, on which the tables weigh most."""
+import pytest
+
+SMALL = 1 << 10        # reduction slot, dt, flag, dynamic coefficients
+VARS = {("fp64", "stage"): 20, ("fp64", "step"): 22, ("fp32", "stage"): 20, ("fp32", "step"): 27}
+
+
+def _problem(nx, schedule):
+    from cases import problems
+    pb = problems.jet_problem(nx, 11, 14, seed=2, noise=1e-3, thermo_noise=1e-3)
+    pb["params"] = dict(pb["params"], schedule=schedule)
+    return pb
+
+
+def _tables(nx):
+    return 8 * (8 * (11 + 4) * (14 + 4) + 4 * (nx + 4))
+
+
+@pytest.mark.parametrize("nx", [5, 40])
+@pytest.mark.parametrize("precision,schedule", list(VARS))
+def test_bytes_cover_every_buffer(nx, precision, schedule):
+    from paper_2301_00817_amd import binding as B
+    prec = B.LES_FP32_STORAGE if precision == "fp32" else B.LES_FP64
+    p = B.make_params(_problem(nx, schedule)["params"], (nx, 11, 14), prec)
+    vs = B.les_layout(p)[2]
+    ts = 4 if precision == "fp32" else 8
+    assert B.les_device_bytes(p) == VARS[precision, schedule] * vs * ts + 5 * 11 * 14 * 8 + _tables(nx)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx", [5, 40])
+@pytest.mark.parametrize("precision,schedule", list(VARS))
+def test_bytes_held_after_a_step(nx, precision, schedule):
+    import torch
+
+    from _helpers import announce, make_solver
+    from paper_2301_00817_amd import binding as B
+    announce("device bytes", nx, precision, schedule)
+    pb = _problem(nx, schedule)
+    s = make_solver(pb, precision)
+    s.rk5_step(s.pad(pb["Q"].cuda(), dtype=torch.float64), 1)
+    held, bound = s.query()[2], B.les_device_bytes(s.p)
+    s.close()
+    assert abs(held - bound) <= SMALL
