@@ -444,16 +444,20 @@ int les_metrics(les_ctx* c, double* metrics_out, void* stream) {
   const size_t tab_bytes = prod_tab_doubles(c->g) * sizeof(double);
   r = dalloc(c, (void**)&c->prod, tab_bytes, "product-mesh tables");
   if (r != LES_OK) return r;
-  hipError_t e;
+  // the flag is lowered first: the copy into `general` is then the last work on
+  // the stream, waited for whether or not it was enqueued without error
+  hipError_t e = launch_reset(c->maxbits, c->flag, s);
+  if (e != hipSuccess) return hip_fail(c, e, "metrics kernel");
   if (c->p.precision == LES_FP32_STORAGE)
     e = launch_metrics<float>(c->coords, c->cg, (float*)c->M, c->g, metrics_out, c->prod, c->flag, s);
   else
     e = launch_metrics<double>(c->coords, c->cg, (double*)c->M, c->g, metrics_out, c->prod, c->flag, s);
   if (e != hipSuccess) return hip_fail(c, e, "metrics kernel");
   int general = 1;
-  HIP_TRY(c, hipMemcpyAsync(&general, c->flag, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIP_TRY(c, launch_reset(c->maxbits, c->flag, s));
-  HIP_TRY(c, hipStreamSynchronize(s));
+  e = hipMemcpyAsync(&general, c->flag, sizeof(int), hipMemcpyDeviceToHost, s);
+  const hipError_t es = hipStreamSynchronize(s);
+  if (e != hipSuccess || es != hipSuccess)
+    return hip_fail(c, e != hipSuccess ? e : es, "reading the product-mesh flag");
   if (general) {
     HIP_TRY(c, hipFree(c->prod));
     c->prod = nullptr;
