@@ -198,7 +198,9 @@ int les_device_bytes(const les_params* p, size_t* bytes);
  * if set to a positive integer, overrides the number of azimuthal planes
  * one block of the fused kernel marches over (tuning and tests); with
  * LESJET_POISON=1 every device buffer the library allocates is filled with
- * NaN bit patterns (a test hook that exposes reads of unwritten memory).
+ * NaN bit patterns (a test hook that exposes reads of unwritten memory); with
+ * LESJET_GENERAL=1 les_metrics makes no tables for a product mesh, which then
+ * takes the kernels of any other mesh, as it does when there is no memory for them.
  * Section "Transformation of
  * Coordinates"; the centerline and periodic subsections of "Boundary
  * Conditions". */

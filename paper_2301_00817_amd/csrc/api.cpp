@@ -441,9 +441,13 @@ int les_metrics(les_ctx* c, double* metrics_out, void* stream) {
   hipStream_t s = (hipStream_t)stream;
   int r = dalloc(c, &c->M, (size_t)10 * c->g.vs * storage_size(&c->p), "metrics");
   if (r != LES_OK) return r;
+  // without memory for the tables (or with LESJET_GENERAL=1) the mesh is a general one
   const size_t tab_bytes = prod_tab_doubles(c->g) * sizeof(double);
-  r = dalloc(c, (void**)&c->prod, tab_bytes, "product-mesh tables");
-  if (r != LES_OK) return r;
+  const char* gen = std::getenv("LESJET_GENERAL");
+  if (!gen || gen[0] != '1') {
+    r = dalloc(c, (void**)&c->prod, tab_bytes, "product-mesh tables");
+    if (r != LES_OK && r != LES_ENOMEM) return r;
+  }
   // the flag is lowered first: the copy into `general` is then the last work on
   // the stream, waited for whether or not it was enqueued without error
   hipError_t e = launch_reset(c->maxbits, c->flag, s);
@@ -458,12 +462,12 @@ int les_metrics(les_ctx* c, double* metrics_out, void* stream) {
   const hipError_t es = hipStreamSynchronize(s);
   if (e != hipSuccess || es != hipSuccess)
     return hip_fail(c, e != hipSuccess ? e : es, "reading the product-mesh flag");
-  if (general) {
+  if (!general) {
+    c->pt = prod_tab(c->prod, c->g);
+  } else if (c->prod) {
     HIP_TRY(c, hipFree(c->prod));
     c->prod = nullptr;
     c->bytes -= tab_bytes;
-  } else {
-    c->pt = prod_tab(c->prod, c->g);
   }
   HIP_TRY(c, hipFree(c->coords));
   c->bytes -= (size_t)3 * c->cg.vs * sizeof(double);

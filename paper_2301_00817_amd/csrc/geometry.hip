@@ -114,11 +114,11 @@ __global__ void k_prod_tab(const double* __restrict__ C, CGrid cg, Grid g, doubl
 
 // Metrics at every point of the padded state box; T is the storage type.
 // *general is raised where the product-mesh tables do not give exactly the
-// stored terms (NaN among them).
+// stored terms (NaN among them), or where there are none.
 template <typename T>
 __global__ void k_metrics(const double* __restrict__ C, CGrid cg, T* __restrict__ M, Grid g,
                           double* __restrict__ M64, ProdTab pt, int* __restrict__ general) {
-  bool same = true;
+  bool same = pt.x != nullptr;
   const int NX = g.nx + 2 * NG, NR = g.nr + 2 * NG, NT = g.nth + 2 * NG;
   const long long tot = (long long)NX * NR * NT;
   for (long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x; t < tot;
@@ -152,6 +152,7 @@ __global__ void k_metrics(const double* __restrict__ C, CGrid cg, T* __restrict_
     for (int c = 0; c < 10; ++c) M[(long long)c * g.vs + o] = (T)m[c];
     if (M64)
       for (int c = 0; c < 10; ++c) M64[(long long)c * g.vs + o] = m[c];
+    if (!pt.x) continue;
     double mp[10];
     product_terms(pt.x[(i + NG) * PX_N],
                   pt.yz + (long long)(k + NG) * prod_plane(g) + (j + NG) * PT_N, mp);
@@ -202,8 +203,9 @@ hipError_t launch_metrics(const double* C, const CGrid& cg, T* M, const Grid& g,
   const long long n = (long long)(g.nx + 2 * NG) * (g.nr + 2 * NG) * (g.nth + 2 * NG);
   const ProdTab pt = prod_tab(tab, g);
   const int nt = (g.nr + 2 * NG) * (g.nth + 2 * NG) + g.nx + 2 * NG;
-  hipLaunchKernelGGL(k_prod_tab, dim3(blocks_for(nt, 256)), dim3(256), 0, s, C, cg, g, tab,
-                     tab + (pt.x - tab));
+  if (tab)
+    hipLaunchKernelGGL(k_prod_tab, dim3(blocks_for(nt, 256)), dim3(256), 0, s, C, cg, g, tab,
+                       tab + (pt.x - tab));
   hipLaunchKernelGGL(k_metrics<T>, dim3(grid_stride_blocks(n)), dim3(256), 0, s, C, cg, M, g, M64, pt,
                      general);
   return hipGetLastError();

@@ -13,8 +13,8 @@ hipError_t launch_coords(const double* xyz, const double* tab, double* C, const 
                          const int bc[6], const double period[3][3], hipStream_t s);
 
 // Metric terms on the padded box, and the tables of a product mesh (tab:
-// prod_tab_doubles(g), laid out as ProdTab by prod_tab); *general (device) is
-// raised if the tables do not reproduce every stored term exactly.
+// prod_tab_doubles(g), laid out as ProdTab by prod_tab, or NULL); *general (device)
+// is raised if the tables do not reproduce every stored term exactly, or are NULL.
 template <typename T>
 hipError_t launch_metrics(const double* C, const CGrid& cg, T* M, const Grid& g, double* M64,
                           double* tab, int* general, hipStream_t s);
@@ -23,6 +23,7 @@ inline size_t prod_tab_doubles(const Grid& g) {
 }
 inline ProdTab prod_tab(const double* tab, const Grid& g) {
   ProdTab pt;
+  if (!tab) return pt;
   pt.yz = tab;
   pt.x = tab + (size_t)(g.nth + 2 * NG) * prod_plane(g);
   return pt;
