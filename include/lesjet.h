@@ -196,7 +196,8 @@ int les_device_bytes(const les_params* p, size_t* bytes);
  * The inputs are copied; they may be freed after the call returns
  * (the call synchronises `stream`).  The environment variable LESJET_KCHUNK,
  * if set to a positive integer, overrides the number of azimuthal planes
- * one block of the fused kernel marches over (tuning and tests); with
+ * one block of the fused kernel marches over, and LESJET_TILE, if set to "narrow"
+ * or "wide", the kernel's tile (tuning and tests); with
  * LESJET_POISON=1 every device buffer the library allocates is filled with
  * NaN bit patterns (a test hook that exposes reads of unwritten memory); with
  * LESJET_GENERAL=1 les_metrics makes no tables for a product mesh, which then

@@ -405,6 +405,10 @@ int les_init_grid(les_ctx** out, const les_params* p, const double* xyz, const d
     const int v = std::atoi(kc);
     if (v >= 1) c->plan.kc = v;
   }
+  if (const char* t = std::getenv("LESJET_TILE")) {      // likewise
+    if (!std::strcmp(t, "narrow")) c->plan.wide = false;
+    if (!std::strcmp(t, "wide")) c->plan.wide = true;
+  }
   hipStream_t s = (hipStream_t)stream;
   r = dalloc(c, (void**)&c->coords, (size_t)3 * c->cg.vs * sizeof(double), "coordinates");
   if (r == LES_OK) r = dalloc(c, (void**)&c->maxbits, sizeof(unsigned long long), "reduction slot");
