@@ -77,9 +77,11 @@ __device__ __forceinline__ void load_metrics(const T* M, const Grid& g, unsigned
 // 3-4 % of the steps on 102 M (FP64) and 23.6 M points (FP32).
 constexpr int WAIT_VMEM = 0x0F70;
 
-// The FP64 kernel has registers left at two waves per SIMD: it loads Q^(0)
-// of the output point an iteration ahead (FP32 at 128 VGPRs does not, nor
-// the FP64 last stage of a general mesh, whose registers carry metric terms).
+// On product meshes the FP64 kernel has registers left at two waves per SIMD: it
+// loads Q^(0) of the output point an iteration ahead (FP32 at 128 VGPRs does not;
+// nor do general meshes, whose registers hold two planes of metric terms: with it
+// their stages spilled four to eight VGPRs, a step of a 200^3 curvilinear mesh took
+// 2.79 against 2.70 ms, of 95^3 401 against 388 us).
 template <typename T> struct PrefetchQ0 { static constexpr bool on = sizeof(T) == 8; };
 
 // The last stage of a step evaluates the next step's CFL sum at its output
@@ -215,16 +217,23 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   T met[10], metn[10];   // general mesh: metrics at (i, j, kk), prefetch for kk+1
   T lag[2], lagn[2];     // held (mu + mu_sgs, conductivity), same planes (LAG_READ)
   // the last stage of a general mesh carries the metric terms of plane kk-1 (Sp)
-  // and gives up the border and Q^(0) loads ahead for them; a product mesh has
-  // the terms in LDS and keeps both (the last stage of 5.9 M points 311 -> 280 us)
+  // and gives up the border loads ahead for them (and still spills 4 VGPRs, 9 with
+  // held viscosities); a product mesh has the terms in LDS and keeps the loads (the
+  // last stage of 5.9 M points 311 -> 280 us)
   constexpr bool CS = EPI == EPI_RK_LAST && !PROD;
   constexpr bool DEFER = CS && sizeof(T) == 8;    // loads deferred to free registers
-  constexpr bool PQ0 = EPI != EPI_R && !CS && PrefetchQ0<T>::on;
+  constexpr bool PQ0 = EPI != EPI_R && PROD && PrefetchQ0<T>::on;
   // the own column two planes ahead is loaded after the point phase in FP64
   // (2-4 % faster than at the top of the iteration; with held viscosities
   // 2 % slower) and on general FP32 meshes, at the top otherwise (FP32
   // product meshes: 2 % faster)
   constexpr bool LATE_QN = sizeof(T) == 8 ? LAG == LAG_NONE || CS : !PROD;
+  // general FP32 meshes: the metric terms of the next plane are loaded after the
+  // point phase too where the registers of the early loads would spill (a stage,
+  // two to nine VGPRs: a step of 128^3 598 -> 590 us, with held viscosities 650 ->
+  // 633; a dynamic residual, four: 297 -> 291 us); a residual, which does not spill,
+  // keeps them early (200^3: 252 against 257 us)
+  constexpr bool LATE_MET = !PROD && sizeof(T) == 4 && (EPI == EPI_RK || (EPI == EPI_R && DYN));
   double q0p[5];         // Q^(0) at (i, j, kk-1), loaded at the top of iteration kk
   const double ad_pre = PQ0 ? alpha * (*dtp) : 0.0;
   auto load_lag = [&](int kk, T v[2]) {
@@ -299,7 +308,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     // ahead), in flight during (b)
     if (more) {
       if (!LATE_QN && kk + 2 <= k1 + 1) load_q(Qin, g, oq, kk + 2, Qn);
-      if (!PROD) load_metrics(M, g, oq, kk + 1, metn);
+      if (!PROD && !LATE_MET) load_metrics(M, g, oq, kk + 1, metn);
       else if (has_t) mt = tab(kk + 1);
       if (LAG == LAG_READ) load_lag(kk + 1, lagn);
     }
@@ -374,6 +383,7 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
     // border of the next plane, in flight during the face phase
     T Bn[5];
     if (!DEFER && more && has_b) load_q(Qin, g, oob, kk + 1, Bn);
+    if (LATE_MET && more) load_metrics(M, g, oq, kk + 1, metn);
     if (LATE_QN && more && kk + 2 <= k1 + 1) load_q(Qin, g, oq, kk + 2, Qn);
     __syncthreads();
 
