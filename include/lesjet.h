@@ -279,8 +279,8 @@ int les_rk5_step(les_ctx* c, double* Qn, int32_t nsteps, double dt_fixed,
  *              entrance target (rho, u, v, w, p) is ADDED to it (only when
  *              xi- is an entrance).
  * Gather form without floating-point atomics: results are bitwise
- * reproducible.  Holds 18 scratch variables of the padded layout and the edges of
- * 32 x 8 tiles (1.6 variables on large meshes, at most 6) after the
+ * reproducible.  Holds 18 scratch variables of the padded layout (17 on a product
+ * mesh) and the edges of 32 x 8 tiles (1.6 variables on large meshes, at most 6) after the
  * first call.  Asynchronous on `stream`. */
 int les_residual_vjp(les_ctx* c, double* Q, const double* Rbar, double* Qbar, double* inflow_bar,
                      void* stream);

@@ -5,9 +5,10 @@
 // separately).  FP64, gather form: every output is accumulated by one
 // thread, with no floating-point atomics, so results are deterministic.
 //
-// Passes (18 scratch variables in the padded layout and the tiles' edges):
-//   1. pressure of every padded point; 1 / J^-1, lambda_bar^d and nu^d of
-//      every point of [-1, n]^3 (zero at the other padded points);
+// Passes (18 scratch variables in the padded layout, 17 on a product mesh, and the
+// tiles' edges):
+//   1. pressure of every padded point; lambda_bar^d, nu^d and (general meshes)
+//      1 / J^-1 of every point of [-1, n]^3 (zero at the other padded points);
 //   2. per padded point: cotangents of its G^d, lambda_bar^d, nu^d and W
 //      from the (up to) four faces per direction whose stencil contains it,
 //      then (points of [-1, n]^3) the reverse of the point function; the
@@ -60,17 +61,18 @@ __device__ __forceinline__ double pressure(const double q[5], const Phys<double>
 enum {
   S_LB = 0,    // lambda_bar^d, points of [-1, n]^3
   S_NU = 3,    // nu^d, points of [-1, n]^3
-  S_IV = 6,    // 1 / J^-1, points of [-1, n]^3
-  S_P = 7,     // pressure of every padded point
-  S_PQ = 8,    // state cotangent of the point's own terms and its tile's neighbours
-  S_DZ = 13,   // what the point hands to its zeta neighbours, [-1, n]^3: half the
+  S_P = 6,     // pressure of every padded point
+  S_PQ = 7,    // state cotangent of the point's own terms and its tile's neighbours
+  S_DZ = 12,   // what the point hands to its zeta neighbours, [-1, n]^3: half the
                // cotangents of its central differences (u v w T), the cotangent
                // of a sensor neighbour pressure
+  S_IV = 17,   // 1 / J^-1, points of [-1, n]^3 (general meshes only)
   S_N = 18
 };
+static long long scratch_vars(bool product) { return product ? S_IV : S_N; }
 
 // What a tile's outer points hand across its edges (five values as S_DZ), after
-// the S_N variables: the rows 0 and AT_Y - 1 of each tile along xi, the columns
+// the variables: the rows 0 and AT_Y - 1 of each tile along xi, the columns
 // 0 and AT_X - 1 along eta, of every padded plane.
 constexpr int AT_X = 32, AT_Y = 8;
 struct EdgeMap {
@@ -90,8 +92,8 @@ struct EdgeMap {
   }
 };
 
-size_t vjp_scratch_doubles(const Grid& g) {
-  return (size_t)S_N * g.vs + (size_t)(EdgeMap(g).per_plane() * (g.nth + 2 * NG));
+size_t vjp_scratch_doubles(const Grid& g, bool product) {
+  return (size_t)(scratch_vars(product) * g.vs) + (size_t)(EdgeMap(g).per_plane() * (g.nth + 2 * NG));
 }
 
 // Points of a padded plane by plane and XCD: workgroups are dealt to the
@@ -1058,7 +1060,7 @@ hipError_t launch_residual_vjp(const double* Q, const double* M, const Grid& g,
     hipLaunchKernelGGL(k_adj_prep<false>, dim3(ptm.per_xcd * NXCD), dim3(PT_X * PT_Y), 0, s, Q, M, g, ph,
                        pt, ptm, pkc, SC);
   const int tiles_x = EdgeMap(g).tx;
-  double* const E = SC + (size_t)S_N * g.vs;
+  double* const E = SC + scratch_vars(pt.x != nullptr) * g.vs;
   const PlaneMap tpm = plane_map(tiles_x * ((g.nr + 2 * NG + AT_Y - 1) / AT_Y));
   if (pt.x)
     hipLaunchKernelGGL(k_adj_main<true>, dim3(plane_map_grid(tpm, g)), dim3(256), 0, s, Q, M, g, ph, pt,

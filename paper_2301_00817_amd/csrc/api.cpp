@@ -70,7 +70,7 @@ struct les_ctx {
   void* PT = nullptr;          // point-quantity scratch of the two-pass residual
   double* part = nullptr;      // per-block partial sums of the diagnostics
   double* part_static = nullptr;   // the same in this device's static scratch (no allocation)
-  double* adj = nullptr;       // residual-adjoint scratch (18 variables and the tiles' edges, FP64)
+  double* adj = nullptr;       // residual-adjoint scratch (17 or 18 variables and the tiles' edges, FP64)
   double* adj_stage = nullptr; // RK5-step adjoint: stage states 1..4 and one cotangent (25 vars)
   unsigned long long* maxbits = nullptr;
   double* dt = nullptr;
@@ -789,7 +789,7 @@ int les_diagnostics_noalloc(les_ctx* c, const double* Qn, double* totals, double
 // Qb = (dR/dQ)^T (fr Rb) at Q (ghosts of Q filled here); inflow_bar accumulated.
 static int residual_vjp_into(les_ctx* c, double* Q, const double* Rb, double fr, double* Qb,
                              double* inflow_bar, hipStream_t s) {
-  int r = dalloc(c, (void**)&c->adj, vjp_scratch_doubles(c->g) * sizeof(double),
+  int r = dalloc(c, (void**)&c->adj, vjp_scratch_doubles(c->g, c->pt.x) * sizeof(double),
                  "adjoint scratch");
   if (r != LES_OK) return r;
   hipError_t e = ghosts<double>(c, Q, s);

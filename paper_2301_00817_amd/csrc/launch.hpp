@@ -105,8 +105,8 @@ hipError_t launch_diagnostics(const double* Q, const TM* M, const Grid& g, const
 
 // Residual adjoint (FP64): Qb = (dR/dQ)^T (fr Rb) on the padded layout (ghost
 // entries zero); inflow_bar (5, nth, nr) accumulated when non-null.  Scratch
-// SC of vjp_scratch_doubles(g) doubles; Q's ghosts must be filled.
-size_t vjp_scratch_doubles(const Grid& g);
+// SC of vjp_scratch_doubles doubles (product: the mesh has tables); Q's ghosts must be filled.
+size_t vjp_scratch_doubles(const Grid& g, bool product);
 // Transpose of the axis-row mean (centerline through the nodes) on a
 // cotangent field: the axis row's cotangent is spread over row 1, then zeroed.
 hipError_t launch_centerline_transpose(double* Qb, const Grid& g, hipStream_t s);

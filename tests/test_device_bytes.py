@@ -44,3 +44,25 @@ def test_bytes_held_after_a_step(nx, precision, schedule):
     held, bound = s.query()[2], B.les_device_bytes(s.p)
     s.close()
     assert abs(held - bound) <= SMALL
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("general", [False, True])
+def test_adjoint_scratch_held(general, monkeypatch):
+    """17 variables on a product mesh, 18 on any other, and the edges of 32 x 8 tiles."""
+    import torch
+
+    from _helpers import announce, make_solver
+    announce("adjoint scratch", general)
+    if general:
+        monkeypatch.setenv("LESJET_GENERAL", "1")
+    pb = _problem(40, "stage")
+    s = make_solver(pb)
+    before = s.query()[2]
+    Q = s.pad(pb["Q"].cuda())
+    s.residual_vjp(Q, torch.ones_like(Q))
+    held = s.query()[2] - before
+    s.close()
+    tx, ty = -(-(40 + 4) // 32), -(-(11 + 4) // 8)
+    edges = 10 * ty * 32 * tx + 10 * tx * 8 * ty
+    assert held == 8 * ((18 if general else 17) * s.vs + edges * (14 + 4))
