@@ -89,10 +89,6 @@ hipError_t launch_dt_finalize(unsigned long long* maxbits, double cfl, double dt
 
 hipError_t launch_reset(unsigned long long* maxbits, int* flag, hipStream_t s);
 
-template <typename T, typename TS>
-hipError_t launch_rk_update(const double* Q0, const T* R, TS* Qout, double* Q64out, const Grid& g,
-                            double alpha, const double* dt, hipStream_t s);
-
 // Per-block partial sums of the diagnostics' totals: at most
 // DIAG_MAX_PARTIALS blocks, 5 sums each.
 constexpr int DIAG_MAX_PARTIALS = 2048;

@@ -1,7 +1,7 @@
-// Time-step reduction and Runge-Kutta stage update (section "Time Marching
-// Method", eq. localdt): Q^(l) = Q^(0) - alpha_l dt R(Q^(l-1)) with one
-// global dt = CFL / max over the interior of (lambda_xi + lambda_eta +
-// lambda_zeta).  The maximum is taken with an integer atomic on the bit
+// Time-step reduction of Runge-Kutta steps (section "Time Marching Method", eq.
+// localdt): one global dt = CFL / max over the interior of (lambda_xi +
+// lambda_eta + lambda_zeta); the stage update is the stage kernel's epilogue.  The
+// maximum is taken with an integer atomic on the bit
 // pattern of non-negative doubles, which orders like the values and makes
 // the result independent of scheduling; a NaN sorts above every number so a
 // diverged state cannot hide.
@@ -93,27 +93,6 @@ __global__ void k_reset(unsigned long long* maxbits, int* flag) {
   if (threadIdx.x == 0 && blockIdx.x == 0) { *maxbits = 0ull; *flag = 0; }
 }
 
-// Q_out = Q0 - alpha dt R on the interior; accumulation in FP64.  Q0 and
-// Q_out may be the same array (last stage), so they are not restrict.
-template <typename T, typename TS>
-__global__ void k_rk_update(const double* Q0, const T* __restrict__ R, TS* Qout,
-                            double* Q64out, Grid g, double alpha, const double* __restrict__ dt) {
-  const long long tot = (long long)g.nx * g.nr * g.nth;
-  const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (t >= tot) return;
-  const int i = (int)(t % g.nx);
-  const int j = (int)((t / g.nx) % g.nr);
-  const int k = (int)(t / ((long long)g.nx * g.nr));
-  const int o = g.at(i, j, k);
-  const double ad = alpha * (*dt);
-  for (int c = 0; c < 5; ++c) {
-    const long long oc = (long long)c * g.vs + o;
-    const double v = Q0[oc] - ad * (double)R[oc];
-    Qout[oc] = (TS)v;
-    if (Q64out) Q64out[oc] = v;
-  }
-}
-
 template <typename TM>
 hipError_t launch_first_pass(const double* Q, const TM* M, const Grid& g, const Phys<double>& ph,
                              bool lambda, unsigned long long* maxbits, float* Q32,
@@ -149,26 +128,11 @@ hipError_t launch_reset(unsigned long long* maxbits, int* flag, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <typename T, typename TS>
-hipError_t launch_rk_update(const double* Q0, const T* R, TS* Qout, double* Q64out, const Grid& g,
-                            double alpha, const double* dt, hipStream_t s) {
-  const long long n = (long long)g.nx * g.nr * g.nth;
-  hipLaunchKernelGGL((k_rk_update<T, TS>), dim3(blocks_for(n, 256)), dim3(256), 0, s, Q0, R, Qout,
-                     Q64out, g, alpha, dt);
-  return hipGetLastError();
-}
-
 template hipError_t launch_first_pass<double>(const double*, const double*, const Grid&,
                                               const Phys<double>&, bool, unsigned long long*,
                                               float*, const ProdTab&, hipStream_t);
 template hipError_t launch_first_pass<float>(const double*, const float*, const Grid&,
                                              const Phys<double>&, bool, unsigned long long*,
                                              float*, const ProdTab&, hipStream_t);
-template hipError_t launch_rk_update<double, double>(const double*, const double*, double*,
-                                                     double*, const Grid&, double, const double*,
-                                                     hipStream_t);
-template hipError_t launch_rk_update<float, float>(const double*, const float*, float*, double*,
-                                                   const Grid&, double, const double*,
-                                                   hipStream_t);
 
 }  // namespace lesjet
