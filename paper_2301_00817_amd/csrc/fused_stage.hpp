@@ -237,8 +237,8 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   double q0p[5];         // Q^(0) at (i, j, kk-1), loaded at the top of iteration kk
   const double ad_pre = PQ0 ? alpha * (*dtp) : 0.0;
   auto load_lag = [&](int kk, T v[2]) {
-    // columns beyond [-1, n] read the nearest held column (all of [-1, n]^3
-    // is written at stage 1); no output uses them
+    // columns beyond [-1, n] lie among the ghosts, where stage 1 writes nothing
+    // (it writes [-1, n]^3): what they read is not defined, and no face uses it
     v[0] = gld(visc, g, 0, kk, oq);
     v[1] = gld(visc, g, 1, kk, oq);
   };
