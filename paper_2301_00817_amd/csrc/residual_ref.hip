@@ -58,7 +58,7 @@ __global__ void k_point_pass(const T* __restrict__ Q, const T* __restrict__ M, G
 }
 
 template <typename T>
-__global__ void k_face_pass(const T* __restrict__ Q, const T* __restrict__ M, Grid g, Phys<T> ph,
+__global__ __launch_bounds__(256) void k_face_pass(const T* __restrict__ Q, const T* __restrict__ M, Grid g, Phys<T> ph,
                             const T* __restrict__ PT, T* __restrict__ R) {
   const long long tot = (long long)g.nx * g.nr * g.nth;
   const long long t = blockIdx.x * (long long)blockDim.x + threadIdx.x;
@@ -93,13 +93,13 @@ __global__ void k_face_pass(const T* __restrict__ Q, const T* __restrict__ M, Gr
     // axis face (centerline through the nodes): lambda_bar of row 1 and the
     // three-point fourth difference (W(-1) replaced by W(1))
     const bool axis_face = ph.axis_node && d == 1 && j == 1;
-    face_flux(G[0], G[1], axis_face ? lb[1] : lb[0], lb[1], nu[0], nu[1], V[0], V[1],
+    face_flux2(G[0], G[1], axis_face ? lb[1] : lb[0], lb[1], nu[0], nu[1], V[0], V[1],
               axis_face ? W[2] : W[0], W[1], W[2], W[3], phys_m, ph, Fm);
-    face_flux(G[1], G[2], lb[1], lb[2], nu[1], nu[2], V[1], V[2], W[1], W[2], W[3], W[4], phys_p,
+    face_flux2(G[1], G[2], lb[1], lb[2], nu[1], nu[2], V[1], V[2], W[1], W[2], W[3], W[4], phys_p,
               ph, Fp);
     for (int c = 0; c < 5; ++c) rhs[c] += Fp[c] - Fm[c];
   }
-  const T iV = trcp(M[9LL * g.vs + o]);
+  const T iV = T(0.5) * trcp(M[9LL * g.vs + o]);   // the fluxes are doubled
   const bool axis_row = ph.axis_node && j == 0;   // not advanced
   for (int c = 0; c < 5; ++c) R[(long long)c * g.vs + o] = axis_row ? T(0) : rhs[c] * iV;
 }

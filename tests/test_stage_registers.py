@@ -53,3 +53,23 @@ def test_product_fp64_steps_without_spill(spills):
     for k, v in spills.items():
         if k[0] == "d" and k[5] == "0" and k[6] == "1":
             assert v == 0, (k, v)
+
+
+def test_two_pass_faces_without_spill():
+    """The face pass of the two-pass residual (256-thread blocks)."""
+    from paper_2301_00817_amd import build as b
+    r = subprocess.run([b._hipcc(), *b.CFLAGS, "--cuda-device-only",
+                        "-Rpass-analysis=kernel-resource-usage", "-c",
+                        os.path.join(b.CSRC, "residual_ref.hip"), "-o", os.devnull],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+    found = {}
+    name = None
+    for line in r.stderr.splitlines():
+        m = re.search(r"Function Name: \S*k_face_passI([df])E", line)
+        if m:
+            name = m.group(1)
+        m = SPILL.search(line)
+        if m and name:
+            found[name], name = int(m.group(1)), None
+    assert found == {"d": 0, "f": 0}
