@@ -36,8 +36,8 @@ CFLAGS = [
 # Per-source flags.  The FP64 stage kernel (bound by latency) is scheduled for
 # instruction-level parallelism: 0.7 % less time per launch on MI355X than the
 # default scheduling.  The FP32 stage kernel (residual_fused32*.hip) keeps the
-# default, under which it fits four waves per SIMD without spilling (3 %
-# faster than with the ILP scheduling, which spills).
+# default, under which its residuals and stages 1-4 fit four waves per SIMD
+# without spilling (3 % faster than with the ILP scheduling, which spills).
 _MAX_ILP = ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]
 SOURCE_FLAGS = {"residual_fused.hip": _MAX_ILP, "residual_fused_wide.hip": _MAX_ILP}
 

@@ -37,8 +37,8 @@ namespace lesjet {
 // waves), FP32 32 x 8 (LDS 29 KB, four blocks per CU) or, WIDE, 32 x 16 (55
 // KB, two blocks).  In FP64 the wide tile computes
 // 512 ring-1 columns for 420 outputs, the narrow one 256 for 196 (7 % more):
-// 21.6 against 23.5 ms a step on 102 M points, 440 against 501 us a residual
-// of a 200^3 curvilinear mesh (before the xi faces left LDS the two were
+// 21.3 against 23.4 ms a step on 102 M points, 440 against 495 us a residual
+// of a 200^3 curvilinear mesh (while the xi faces went through LDS the two were
 // within 1 %).  fused_plan picks the tile that a mesh's extents waste less of.
 template <typename T, bool WIDE> struct Tile;
 template <> struct Tile<double, false> { static constexpr int X = 16, Y = 16, PER_CU = 2; };
@@ -104,7 +104,10 @@ template <typename T> struct PrefetchQ0 { static constexpr bool on = sizeof(T) =
 template <typename T> struct WavePrio { static constexpr bool on = sizeof(T) == 8; };
 
 // Register budget: FP64 two waves per SIMD (up to 256 VGPRs), FP32 four
-// (128), three (168) in the last stage of general meshes.
+// (128), three (168) in the last stage of general meshes.  The FP32 last stage of a
+// product mesh spills one VGPR with held viscosities and up to four with the dynamic
+// model, and is still 2-4 % of a step faster than at three waves (256 x 256 x 360,
+// held: 4.28 against 4.36 ms).
 template <typename T> struct FusedOcc;
 template <> struct FusedOcc<double> { static constexpr int waves = 2; };
 template <> struct FusedOcc<float> { static constexpr int waves = 4; };
@@ -123,13 +126,13 @@ template <> struct FusedOccE<float, EPI_RK_LAST, false> { static constexpr int w
 // values per (j, k), staged in LDS once per plane and tile row by threads that
 // hold no border point, three per i), which spares 80 of the 200 bytes per
 // point and stage (FP32: 40 of 128), the registers of two planes of metric
-// terms, and the arithmetic on the four terms that are zero.  The terms and results are bitwise those of the general
-// form in FP64 (the derived values within two ulps).  A step (with the first reduction of dt, which reads the same
-// tables): 36.7 -> 28.4 ms on 102 M points, 4.21 -> 3.61 ms for two on 5.9 M,
-// FP32 5.77 -> 4.83 ms on 23.6 M.  The derived values (FP64 only: the FP32
-// hardware reciprocal, root and logarithm cost no more than the products)
-// spare a reciprocal, two roots and a cube root of the 850 vector operations
-// per point and plane: another 3 % (24.0 -> 23.1 ms on 102 M points).
+// terms, and the arithmetic on the four terms that are zero.  The terms are bitwise those
+// stored, the derived values within two ulps of those computed from them.  The same
+// meshes with the terms read against the tables: a step of 102 M points 31.5 / 21.2
+// ms, two of 5.9 M 3.71 / 2.66 ms, FP32 on 23.6 M 5.59 / 4.00 ms.  The derived values
+// (FP64 only: the FP32 hardware reciprocal, root and logarithm cost no more than
+// the products) spare a reciprocal, two roots and a cube root of the 850 vector
+// operations per point and plane: 4 % of that (22.1 and 2.75 ms without them).
 template <typename T, bool WIDE, int EPI, bool AXIS, int LAG, bool DYN, bool PROD>
 __global__ void __launch_bounds__((Tile<T, WIDE>::X * Tile<T, WIDE>::Y), (FusedOccE<T, EPI, PROD>::waves))
 k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_arg, int kc,
@@ -162,9 +165,9 @@ k_fused(const T* __restrict__ Qin, const T* __restrict__ M, Grid g, Phys<T> ph_a
   // through LDS: LDS was busy 45 % of the FP64 kernel's time when it carried
   // both (and the thread's own values back to it), a moved double costs two
   // vector moves on one of the four SIMDs against eight cycles of the CU's
-  // LDS.  102 M points: LDS 6.2 -> 3.5 M cycles per CU and launch, the stage
-  // 5.68 -> 5.21 ms; residual of a 95^3 mesh 74.0 -> 68.4 us, FP32 step on
-  // 23.6 M points 4.83 -> 4.54 ms.
+  // LDS.  When the xi faces left it: LDS 6.2 -> 3.5 M cycles per CU and launch on
+  // 102 M points, the stage 8 % shorter, a residual of a 95^3 mesh 8 %, an FP32
+  // step on 23.6 M points 6 %.
   __shared__ T sFe[5][FB_Y][FB_X];
   __shared__ double sRed[(FB_X * FB_Y + 63) / 64];
   // product mesh: table rows of the planes kk-1 .. kk+1 (slot = plane mod 4)
@@ -593,9 +596,10 @@ FusedPlan tile_plan(const Grid& g, int num_cu, double* cost_out) {
   }
   choose(64);
   if (best_blocks > resident) choose(32);
-  // four waves alone on a CU take a plane in about 0.8 of the time of eight
-  // (16^3, every block alone on its CU: 13.4 against 14.8 us, 7 us of them the
-  // launches)
+  // four waves alone on a CU take a plane in about 0.8 of the time of eight (12
+  // meshes of 9^3 to 60 x 14 x 14 whose narrow blocks are each alone on a CU: a step
+  // 6-11 % shorter with the narrow tile on every one, at equal rounds and planes;
+  // eight of 32^3 to 48^3 with 288 to 384 narrow blocks: 0.5-4 % longer)
   if (!WIDE && best_blocks <= num_cu) *cost_out *= 0.8;
   return best;
 }

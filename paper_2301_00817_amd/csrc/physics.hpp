@@ -281,8 +281,9 @@ __host__ __device__ __forceinline__ T filter_sq(T x, const PointIn<T>& in) {
 // into one factor, the root's shorter iteration and no default values for
 // threads without a face, the stage kernel's vector operations per point and
 // plane fell from 942 to 856 (the FP64 kernel is held back by power as well as
-// latency: its clock fell from 2.2 to 1.8 GHz as its stalls went): a step on 102 M
-// points 24.7 -> 23.8 ms, the residual of a 95^3 mesh 59.8 -> 56.7 us.
+// latency: its clock fell from 2.2 to 1.8 GHz as its stalls went): 4 % of a step
+// on 102 M points then, 5 % of the residual of a 95^3 mesh (now 21.2 ms, and 66 us
+// with states in turn, 57 on one state again and again).
 template <typename T, int LAG = LAG_NONE, bool DYN = false, bool PROD = false, bool STAGE = false>
 __host__ __device__ inline void point_quantities(const PointIn<T>& in, const Phys<T>& ph,
                                                  PointOut<T>& out) {

@@ -14,10 +14,10 @@ extern template hipError_t launch_fused_tile<double, true>(
 
 // The tile that takes fewer (rounds) x (planes per block); the wide one on a
 // tie, as it computes fewer halo columns.  Narrow against wide, a residual:
-// 16^3 13.4 / 14.8 us, 61 x 43 x 50 23.8 / 25.5 us (narrow chosen); 32^3
-// curvilinear 17.4 / 17.2 us, 64^3 27.1 / 26.1 us, 173 x 67 x 90 60.5 / 56.3
-// us, 29 x 200 x 200 89 / 68 us, 128^3 curvilinear 142 / 133 us, 320 x 200 x
-// 160 459 / 416 us, 200^3 curvilinear 503 / 437 us (wide chosen).
+// 16^3 13.8 / 15.0 us, 61 x 43 x 50 24.5 / 25.9 us (narrow chosen); 32^3
+// curvilinear 17.8 / 17.6 us, 64^3 curvilinear 31.9 / 31.4 us, 173 x 67 x 90 60.7 /
+// 56.8 us, 29 x 200 x 200 89 / 69 us, 128^3 curvilinear 141 / 133 us, 320 x 200 x
+// 160 459 / 416 us, 200^3 curvilinear 495 / 440 us (wide chosen).
 template <>
 FusedPlan fused_plan<double>(const Grid& g, int num_cu) {
   double cn, cw;

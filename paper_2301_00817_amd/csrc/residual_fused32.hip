@@ -1,8 +1,8 @@
 // The RK stage kernel in the FP32-storage form (FP32 stage states, metrics
 // and fluxes; FP64 Q^(0) and stage accumulation), narrow tile, and the choice of
 // the tile.  The kernel template is in fused_stage.hpp; the FP32 translation
-// units keep the default instruction scheduling, under which the kernel fits
-// four waves per SIMD without spilling.
+// units keep the default instruction scheduling, under which residuals and stages
+// 1-4 fit four waves per SIMD without spilling.
 #include "fused_stage.hpp"
 
 namespace lesjet {
@@ -15,12 +15,12 @@ extern template hipError_t launch_fused_tile<float, true>(
 // The chunk length is the narrow tile's (states depend on it by their rounding,
 // not on the tile: the two give the same bits); the wide tile, which computes 14 %
 // fewer columns but keeps eight waves in step, where it saves a round of
-// blocks.  Narrow against wide, a step: 222^3 curvilinear 2.72 / 2.61 ms (5 / 4
-// rounds), 300 x 210 x 200 2.14 / 2.05 (7 / 6), 256 x 256 x 360 4.11 / 4.05 (10 /
-// 9), 320^3 curvilinear 7.53 / 7.23 (12 / 10), 512 x 256 x 360 8.00 / 7.67 (20 /
-// 18), 800 x 400 x 320 16.57 / 15.98 (36 / 31) (wide chosen); 61 x 43 x 50 0.187 /
-// 0.192, 95^3 curvilinear 0.314 / 0.324 (1 / 1), 288 x 160 x 128 1.10 / 1.12 (3 /
-// 3), 256^3 curvilinear 4.11 / 4.14 (7 / 7) (narrow chosen).
+// blocks.  Narrow against wide, a step: 222^3 curvilinear 2.51 / 2.42 ms (5 / 4
+// rounds), 300 x 210 x 200 2.08 / 2.01 (7 / 6), 256 x 256 x 360 4.01 / 4.01 (10 /
+// 9), 320^3 curvilinear 6.93 / 6.82 (12 / 10), 512 x 256 x 360 7.57 / 7.46 (20 /
+// 18), 800 x 400 x 320 15.75 / 15.10 (36 / 31) (wide chosen); 61 x 43 x 50 0.184 /
+// 0.188, 95^3 curvilinear 0.308 / 0.317 (1 / 1), 288 x 160 x 128 1.06 / 1.09 (3 /
+// 3), 256^3 curvilinear 3.90 / 3.89 (7 / 7) (narrow chosen).
 template <>
 FusedPlan fused_plan<float>(const Grid& g, int num_cu) {
   double cost;
