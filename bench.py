@@ -20,13 +20,20 @@ The JSON line also carries
                stage taken as its two steps, residual (read the stage state
                and the metrics, write R) and update (read Q^(0) and R, write
                the new stage state): FP64 280 B, FP32 storage 168 B averaged
-               over the five stages.  `fused` gives the same kernel against
-               the bytes it moves itself (R never leaves the chip: 200 B,
-               FP32 storage 128 B; 80 B and 40 B less on a product mesh, whose
-               metric terms are not read).  `traffic` is the HBM bytes per launch
-               measured by rocprofv3 FETCH_SIZE + WRITE_SIZE
+               over the five stages.  This is a rate of the method, not of the
+               memory bus: the kernel keeps R on the chip and, on the
+               product meshes timed here, forms the metric terms from tables, so it
+               moves less than half of these bytes and may pass the streaming
+               rate.  `fused` gives the same launches against the bytes the
+               kernel moves at least (FP64 120 B, FP32 storage 88 B; 200 B and
+               128 B on a mesh whose metric terms are read), `traffic` the HBM
+               bytes per launch measured by rocprofv3 FETCH_SIZE + WRITE_SIZE
                (profiles/traffic.json) when those counters were taken on the
-               current kernel sources and on this workload, else null;
+               current kernel sources and on this workload, else null, and
+               `moved` their rate.  `bound` is "hbm" where the metric terms
+               are read and "issue" on product meshes, whose memory moves at
+               half its rate: FP32 issues vector operations in 90 % of its
+               slots, FP64 in half of them at a clock held down by power;
                `stream_GBs` the rate of a plain elementwise streaming kernel
                (4 GiB read and written) measured in the same run, the
                achievable bandwidth beside the nominal peak;
@@ -73,9 +80,10 @@ METHOD_STAGE_BYTES = {"fp64": 280.0, "fp32": 168.0}
 # state (5) and the metrics (10), read Q^(0) (5 FP64), write the stage state
 # (5).  FP64: 200 B.  FP32 storage: 20 + 40 + 40 + 20 = 120 B, plus 40 B for
 # the FP64 Q^(n+1) in the last stage, i.e. 128 B averaged over the stages.
-# A product mesh (every jet here) forms the metric terms from tables and moves
-# 80 B (FP32 storage 40 B) less; the figures stay those of a general mesh.
+# A product mesh (every workload here) forms the metric terms from tables and
+# moves 80 B (FP32 storage 40 B) less.
 FUSED_STAGE_BYTES = {"fp64": (5 + 10 + 5 + 5) * 8.0, "fp32": (5 + 10 + 5) * 4 + 5 * 8 + 5 * 8 / 5}
+METRIC_BYTES = {"fp64": 10 * 8.0, "fp32": 10 * 4.0}
 # The per-step update schedule (viscosities held from stage 1) adds two
 # values per point: written by the first stage, read by the four others.
 HELD_VISC_BYTES = {"fp64": 2 * 8, "fp32": 2 * 4}
@@ -348,7 +356,7 @@ def main():
     value = npts * 5 * args.steps / r["wall"] / 1e6
     workload = f"{args.config}-{args.precision}" + ("-step" if args.schedule == "step" else "")
     roof = roofline(args.precision, args.schedule == "step" and prm["visc_coef"] != 0.0, npts,
-                    r, workload)
+                    r, workload, product=True)
 
     out = {
         "metric": METRIC,
@@ -384,7 +392,8 @@ def main():
         v2 = npts * 5 * args.steps / r2["wall"] / 1e6
         fp32_v, fp64_v = (v2, value) if other == "fp32" else (value, v2)
         roof2 = roofline(other, args.schedule == "step" and prm["visc_coef"] != 0.0, npts, r2,
-                         f"{args.config}-{other}" + ("-step" if args.schedule == "step" else ""))
+                         f"{args.config}-{other}" + ("-step" if args.schedule == "step" else ""),
+                         product=True)
         out["precision_forms"] = {"fp64": round(fp64_v, 2), "fp32": round(fp32_v, 2),
                                   "fp32_over_fp64": round(fp32_v / fp64_v, 3),
                                   "unit": "Mpoint-RK-stage updates/s",
@@ -403,6 +412,8 @@ def main():
         for rf in (out["roofline"], out["precision_forms"][other + "_run"]["roofline"]):
             rf["stream_GBs"] = stream
             rf["frac_of_stream"] = round(rf["achieved"] / stream, 4)
+            if rf["moved"]:
+                rf["moved"]["frac_of_stream"] = round(rf["moved"]["achieved"] / stream, 4)
     if not args.no_cpu_baseline:
         print("[bench] cpu baseline (oracle)", file=sys.stderr, flush=True)
         out["cpu_baseline"] = cpu_baseline()
@@ -411,23 +422,26 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-def roofline(precision, held, npts, r, workload):
-    """Roofline object of the stage kernel from a time_rk result."""
+def roofline(precision, held, npts, r, workload, product=False):
+    """Roofline object of the stage kernel from a time_rk result; product:
+    the mesh's metric terms come from tables."""
     avg_ms = r["kernel_ms"] / max(r["launches"], 1)
     extra = HELD_VISC_BYTES[precision] if held else 0
     method_bytes = (METHOD_STAGE_BYTES[precision] + extra) * npts
-    fused_bytes = (FUSED_STAGE_BYTES[precision] + extra) * npts
-    achieved = method_bytes / (avg_ms * 1e-3) / 1e9
-    fused = fused_bytes / (avg_ms * 1e-3) / 1e9
-    return {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-            "frac": round(achieved / PEAK_HBM_GBS, 4),
-            "traffic": traffic_for(DOMINANT_KERNEL, workload),
+    fused_point = FUSED_STAGE_BYTES[precision] + extra - (METRIC_BYTES[precision] if product else 0)
+    traffic = traffic_for(DOMINANT_KERNEL, workload)
+
+    def rate(nbytes):
+        gbs = nbytes / (avg_ms * 1e-3) / 1e9
+        return {"achieved": round(gbs, 1), "frac": round(gbs / PEAK_HBM_GBS, 4)}
+
+    return {"bound": "issue" if product else "hbm", **rate(method_bytes), "peak": PEAK_HBM_GBS,
+            "unit": "GB/s", "traffic": traffic, "moved": rate(traffic) if traffic else None,
             "kernel": DOMINANT_KERNEL, "avg_launch_ms": round(avg_ms, 4),
             "launches": r["launches"],
             "algorithmic_bytes_per_point": METHOD_STAGE_BYTES[precision] + extra,
             "algorithmic_bytes_per_launch": method_bytes,
-            "fused": {"bytes_per_point": FUSED_STAGE_BYTES[precision] + extra,
-                      "achieved": round(fused, 1), "frac": round(fused / PEAK_HBM_GBS, 4)}}
+            "fused": {"bytes_per_point": fused_point, **rate(fused_point * npts)}}
 
 
 SGS_MODELS = {"none": 0, "smagorinsky": 1, "vreman": 2, "dynamic": 3}
