@@ -36,15 +36,13 @@ def _problem(shape, kind, sgs, schedule):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("general", [False, True])
-@pytest.mark.parametrize("shape,kind,sgs,schedule", [
-    ((31, 15, 18), "jet", 1, "stage"), ((32, 17, 12), "jet", 2, "step"),
-    ((31, 15, 16), "node", 1, "stage"), ((33, 9, 12), "node", 2, "step"),
-    ((33, 17, 11), "box", 3, "stage"), ((17, 33, 11), "box", 3, "step"),
-    ((17, 17, 17), "wavy", 1, "stage"), ((33, 33, 33), "wavy", 2, "step")])
+@pytest.mark.parametrize("shape,kind,sgs,schedule,general", [
+    *(c + (g,) for g in (False, True) for c in (
+        ((31, 15, 18), "jet", 1, "stage"), ((32, 17, 12), "jet", 2, "step"),
+        ((31, 15, 16), "node", 1, "stage"), ((33, 9, 12), "node", 2, "step"),
+        ((33, 17, 11), "box", 3, "stage"), ((17, 33, 11), "box", 3, "step"))),
+    ((17, 17, 17), "wavy", 1, "stage", True), ((33, 33, 33), "wavy", 2, "step", True)])
 def test_both_tiles(shape, kind, sgs, schedule, general, precision, monkeypatch):
-    if general and kind == "wavy":
-        pytest.skip("a general mesh already")
     announce("tile forms", shape, kind, sgs, schedule, general, precision)
     pb = _problem(shape, kind, sgs, schedule)
     prm = pb["params"]
